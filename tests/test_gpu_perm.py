@@ -49,6 +49,42 @@ def test_permute_matches_definition(nsd, n, inverse):
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("n", [300 * 32768 + 77])  # more than 256 windows: two digit passes
+@pytest.mark.parametrize("kind", ["random", "identity", "reverse", "swapped"])
+@pytest.mark.parametrize("inverse", [0, 1])
+def test_plan_build_many_windows(nsd, n, kind, inverse):
+    rng = np.random.default_rng(5)
+    perm = {"random": lambda: rng.permutation(n), "identity": lambda: np.arange(n),
+            "reverse": lambda: np.arange(n)[::-1].copy(),
+            "swapped": lambda: np.concatenate([np.arange(n // 2, n), np.arange(n // 2)])}[kind]()
+    src = rng.integers(0, 2**31, n, dtype=np.int32).view(np.float32)
+    got = run_perm(nsd, perm, src, inverse)
+    want = np.empty_like(src)
+    if inverse:
+        want[perm] = src
+    else:
+        want = src[perm]
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("where", [(0, 1), (0, 99_999), (40_000, 70_000), (99_998, 99_999)])
+def test_perm_plan_rejects_a_repeated_index(nsd, inverse, where):
+    """One index given twice (so one is missing), in one window of 32,768 or
+    in two, and one out of range."""
+    from paper_2303_07030_amd.operand import build_perm_plan
+    n = 100_000
+    perm = np.random.default_rng(1).permutation(n)
+    inv = np.argsort(perm)
+    a, b = where
+    for value in (a, n, -1, 2**31 - 1):
+        bad = perm.copy()
+        bad[inv[b]] = value
+        with pytest.raises(nsd.NsdError) as e:
+            build_perm_plan(n, torch.from_numpy(bad.astype(np.int32)).cuda(), inverse, "cuda")
+        assert e.value.status == nsd.NSD_ERR_BAD_FORMAT
+
+
 def test_permute_csr_to_csc_and_back(nsd):
     """The CSC permutation of a power-law pattern (long rows whose entries
     spread over all columns) both ways: values into CSC order and back."""
