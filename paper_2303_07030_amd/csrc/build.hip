@@ -22,10 +22,6 @@ struct OpSum {
     static constexpr int kIdentity = 0;
     __device__ static int apply(int a, int b) { return a + b; }
 };
-struct OpMax {
-    static constexpr int kIdentity = INT32_MIN;
-    __device__ static int apply(int a, int b) { return a > b ? a : b; }
-};
 
 // Exclusive scan of one value per thread across the block; returns the
 // block total through *total.
@@ -162,12 +158,6 @@ nsd_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *t
                           void *ws, hipStream_t st) {
     Carver c(ws);
     return scan_level<OpSum>(in, out, n, total_dev, c, st);
-}
-
-nsd_status scan_exclusive_max(const int32_t *in, int32_t *out, int64_t n, void *ws,
-                              hipStream_t st) {
-    Carver c(ws);
-    return scan_level<OpMax>(in, out, n, nullptr, c, st);
 }
 
 // ------------------------------------------------------------ radix sort
