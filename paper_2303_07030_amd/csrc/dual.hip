@@ -24,6 +24,8 @@
 // (perm[p] for a CSC pass), so the sampled product is written aligned with
 // A's own pattern.  Up to two passes share one launch on disjoint block
 // ranges; long segments leave chunk partials combined by the shared kernel.
+#include <algorithm>
+
 #include "nsd_internal.hpp"
 #include "segreduce.hpp"
 #include "segreduce_dev.hpp"
@@ -257,6 +259,8 @@ int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k, bool vec) {
     int64_t n = 0;
     for (int i = 0; i < npass; ++i)
         n += ceil_div(plans[i]->nitems, slots) + ceil_div(plans[i]->nempty, slots);
+    if (k == 1)  // a linear pass runs by tiles (vec1.hip)
+        for (int i = 0; i < npass; ++i) n = std::max(n, vec1_max_tiles(*plans[i]));
     return n;
 }
 

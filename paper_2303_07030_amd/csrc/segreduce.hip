@@ -56,9 +56,11 @@ __global__ void fill_zero_kernel(float *out, int64_t n) {
     if (i < n) out[i] = 0.f;
 }
 
-// One partial row per chunk item (compact, see store_chunk_partial).
+// One partial row per chunk item (compact, see store_chunk_partial); at width
+// 1 the two words per tile of vec1.hip's passes, where those are more.
 size_t sgr_part_bytes(const nsd_plan &plan, int k) {
-    return (size_t)std::max<int64_t>(plan.nchunks, 1) * (size_t)k * sizeof(float);
+    const size_t chunks = (size_t)std::max<int64_t>(plan.nchunks, 1) * (size_t)k * sizeof(float);
+    return k > 1 ? chunks : std::max(chunks, 2 * sizeof(float) * (size_t)vec1_max_tiles(plan));
 }
 
 template <int VEC, int G>
@@ -88,6 +90,7 @@ nsd_status segreduce(SgrParams a, hipStream_t st) {
         if (total > 0) fill_zero_kernel<<<ceil_div(total, 256), 256, 0, st>>>(a.out, total);
         return check_launch("fill_zero_kernel");
     }
+    if (a.k == 1) return vec1_reduce(a, LossJob{}, st);
     // float4 lanes need 16-byte aligned dense rows; otherwise use scalar lanes
     const WidthPlan wp = width_plan(a.k, aligned16(a.out) && (!a.X || aligned16(a.X)));
     SgrLauncher f{a, st};
@@ -186,6 +189,12 @@ int choose_slot_len(int64_t nnz, int slots_per_wave) {
 SddmmShape sddmm_shape(int64_t nnz, int k, bool vec_ok) {
     SddmmShape sh;
     sh.wp = width_plan(k, vec_ok);
+    if (k == 1) {  // entry by entry (vec1.hip): a slot is a thread's entries
+        sh.L = kVec1SddmmEntries;
+        sh.nslots = ceil_div(nnz, sh.L);
+        sh.nblocks = ceil_div(sh.nslots, kBlock);
+        return sh;
+    }
     const int slots_per_block = kBlock / sh.wp.g;
     sh.L = choose_slot_len(nnz, kWave / sh.wp.g);
     sh.nslots = nnz > 0 ? ceil_div(nnz, sh.L) : 0;
@@ -213,6 +222,7 @@ nsd_status sddmm(SddmmParams a, hipStream_t st) {
     a.L = sh.L;
     a.nslots = (int32_t)sh.nslots;
     if (sh.nblocks == 0) return NSD_OK;
+    if (a.k == 1) return vec1_sddmm(a, sh.nblocks, st);
     SddmmLauncher f{a, sh.nblocks, st};
     return dispatch_width(sh.wp, f);
 }

@@ -16,7 +16,7 @@ struct SgrParams {
     const float *X = nullptr;         // gathered dense operand (NULL: ones)
     float alpha = 1.f;
     float *out = nullptr;             // [nseg x k]
-    float *part = nullptr;            // [plan.nitems x k] chunk partials
+    float *part = nullptr;            // chunk partials (sgr_part_bytes)
     // Rows of `part` that hold a long segment's partials: its first chunk's
     // and, past it, those of the chunks at item indexes divisible by
     // chunk_stride (1: every chunk's; chunk_group<G>(): one per group of
@@ -47,6 +47,9 @@ struct SddmmShape {
 };
 
 int choose_slot_len(int64_t nnz, int slots_per_wave);
+
+// Entries per thread of the width-1 sampled product.
+constexpr int kVec1SddmmEntries = 8;
 size_t sgr_part_bytes(const nsd_plan &plan, int k);
 nsd_status segreduce(SgrParams a, hipStream_t st);
 
@@ -136,6 +139,18 @@ nsd_status frob_fused(FrobParams f, hipStream_t st);
 SddmmShape sddmm_shape(int64_t nnz, int k, bool vec_ok);
 bool sddmm_vec_ok(const SddmmParams &a);
 nsd_status sddmm(SddmmParams a, hipStream_t st);
+
+// Width-1 passes (vec1.hip): the gather-reduce (with a loss total of earlier
+// partials on its combine launch), the linear dual pass (a job without p1
+// sums the pass's own loss; `entries`: the operand's rows, columns and values
+// in its own order with the dense operands, from which a small pass forms it)
+// and the sampled product in `nblocks` blocks.
+// vec1_max_tiles bounds the tiles, one loss partial and two floats each.
+nsd_status vec1_reduce(const SgrParams &a, LossJob job, hipStream_t st);
+nsd_status vec1_dual(const DualPass &m, const SddmmParams &entries, double *loss_part,
+                     int probe_id, LossJob job, hipStream_t st);
+nsd_status vec1_sddmm(const SddmmParams &a, int64_t nblocks, hipStream_t st);
+int64_t vec1_max_tiles(const nsd_plan &plan);
 
 nsd_status loss_finalize(const double *part, int64_t n, double *loss, hipStream_t st);
 
