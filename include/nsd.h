@@ -505,11 +505,10 @@ nsd_status nsd_loss_bilinear_noalloc(const nsd_csr *A, const nsd_csc *At, const 
  * A's CSR gives the row pass (values A->val), its CSC the column pass with
  * the values in CSC order valT [nnz] (nsd_gather_f32 of A->val by At->perm,
  * made once when A is data; NULL: read A->val through At->perm each call).
- * U, dU [nrows x k]; V, dV [ncols x k].  Any k >= 1: up to 256 (multiple of
- * 4, 16-byte aligned rows) or up to 64 otherwise, both passes run fused in
- * one launch; a wider k forms r once per stored entry in the workspace (its
- * size query counts nnz floats for every k > 64) and runs the two
- * gather-reduces with r as weights.  Async.
+ * U, dU [nrows x k]; V, dV [ncols x k].  Any k >= 1: up to 256 both passes
+ * run fused in one launch; a wider k forms r once per stored entry in the
+ * workspace (its size query counts nnz floats for every k > 256) and runs the
+ * two gather-reduces with r as weights.  Async.
  */
 nsd_status nsd_loss_mf(const nsd_csr *A, const nsd_csc *At, const float *valT, const float *U,
                        const float *V, int32_t k, float seed, double *loss, float *dU, float *dV,
@@ -529,10 +528,10 @@ nsd_status nsd_cp_workspace_size(const nsd_coo3 *X, int32_t rank, size_t *bytes)
  *   dX [nnz] = seed * R, aligned with X's input order (X->mode[n].perm)
  *   dF1[i,:] = -seed sum R_ijl (F2[j,:] o F3[l,:]), cyclically dF2, dF3
  *   (the negated mode-n MTTKRPs of R).
- * Any rank >= 1: up to 256 (multiple of 4, 16-byte aligned rows) or up to 64
- * otherwise, the three mode passes run fused in one launch; a wider rank
- * forms R once in the workspace (counted by nsd_cp_workspace_size for every
- * rank > 64) and runs one gather-reduce per mode with R as weights.  Async.
+ * Any rank >= 1: up to 256 the three mode passes run fused in one launch; a
+ * wider rank forms R once in the workspace (counted by nsd_cp_workspace_size
+ * for every rank > 256) and runs one gather-reduce per mode with R as
+ * weights.  Async.
  */
 nsd_status nsd_loss_cp(const nsd_coo3 *X, const float *F1, const float *F2, const float *F3,
                        int32_t rank, float seed, double *loss, float *dX, float *dF1,
@@ -714,9 +713,8 @@ nsd_status nsd_cpn_workspace_size(const nsd_coon *X, int32_t rank, size_t *bytes
  *   dF_n(c_n, :) = -seed sum R * (o_{m != n} F_m(c_m, :))  (negated MTTKRPs).
  * F and dF are HOST arrays of `order` device pointers to [dims[n] x rank]
  * row-major factors.  *loss (device fp64) is not scaled by seed.  Any
- * rank >= 1; ranks above 256 (above 64 without 16-byte aligned rows of a
- * multiple of 4) form R once in the workspace and run one gather-reduce per
- * mode.  Async.
+ * rank >= 1; ranks above 256 form R once in the workspace and run one
+ * gather-reduce per mode.  Async.
  */
 nsd_status nsd_loss_cpn(const nsd_coon *X, const float *const *F, int32_t rank, float seed,
                         double *loss, float *dX, float *const *dF, void *ws, size_t ws_bytes,

@@ -60,20 +60,18 @@ static size_t part_region_bytes(const nsd_csr *A, const nsd_csc *At, int k) {
 
 static size_t loss_part_count(const nsd_csr *A, const nsd_csc *At, int k) {
     int64_t m = std::max<int64_t>(1, frob_row_blocks(A->plan, k));
-    for (int kk : {k, 1})
-        for (bool v : {true, false}) m = std::max(m, sddmm_shape(A->nnz, kk, v).nblocks);
+    for (int kk : {k, 1}) m = std::max(m, sddmm_shape(A->nnz, kk).nblocks);
     if (At) {
         const nsd_plan *both[2] = {&A->plan, &At->plan};
-        for (bool v : {true, false}) m = std::max(m, dual_blocks(both, 2, k, v));
+        m = std::max(m, dual_blocks(both, 2, k));
     }
     return (size_t)m;
 }
 
-// Widths that a fused factorisation pass may not hold (above 64 columns
-// without float4 rows, above 256 with them) form the residual once, one
-// float per stored entry.
+// Widths that a fused factorisation pass does not hold form the residual
+// once, one float per stored entry.
 static size_t resid_buf_bytes(const nsd_csr *A, int k) {
-    return k > 64 ? round256((size_t)std::max(A->nnz, 1) * sizeof(float)) : 0;
+    return k > kMaxFusedWidth ? round256((size_t)std::max(A->nnz, 1) * sizeof(float)) : 0;
 }
 
 // A CSC carrying both two-pass forms of its perm moves A's values to CSC
@@ -211,12 +209,6 @@ static nsd_status col_dual_run(const nsd_csr *A, const DualPass &pass, double *l
     return dual_fused(kDualLin, f, NSD_KERNEL_DUAL, job, st);
 }
 
-static bool col_dual_ok(const DualPass &pass) {
-    DualParams f;
-    f.pass[0] = pass;
-    return dual_supported(pass.s.k, dual_vec_ok(f));
-}
-
 // From this many entries on the SMVM loss streams A's entries (dA and the
 // loss) and reads only the values through the CSC; below, one column pass
 // does it all, with its scattered words of dA in cache and a launch less.
@@ -241,10 +233,7 @@ static nsd_status check_bilinear(const nsd_csr *A, const nsd_csc *At, const floa
 // pass, or of the unfused SDDMM (widths a fused slot does not hold).
 static int64_t bilinear_loss_parts(const nsd_csr *A, const nsd_csc *At, int k) {
     const nsd_plan *cols[1] = {&At->plan};
-    int64_t m = 1;
-    for (bool v : {true, false})
-        m = std::max({m, dual_blocks(cols, 1, k, v), sddmm_shape(A->nnz, k, v).nblocks});
-    return m;
+    return std::max<int64_t>({1, dual_blocks(cols, 1, k), sddmm_shape(A->nnz, k).nblocks});
 }
 
 // The loss total of an unfused SDDMM's block partials; with nnz == 0 the
@@ -284,7 +273,7 @@ static nsd_status bilinear_run(const nsd_csr *A, const nsd_csc *At, const float 
         // one pass over the columns: own row H_j, gathered row G_i:
         // dA[p] = seed <G_i, H_j>, loss = sum_p A_p <G_i, H_j>, dH = seed A^T G
         DualPass pass = col_dual(A, At, G, H, k, seed, dH, part_col, dA, seed, true);
-        if (col_dual_ok(pass)) {
+        if (k <= kMaxFusedWidth) {
             NSD_TRY(csc_order_before(A, At, valT, gradT, staging, pass, st));
             NSD_TRY(col_dual_run(A, pass, loss_part, loss, st));
             return csc_order_after(At, valT, gradT, staging, dA, st);
@@ -333,7 +322,7 @@ static nsd_status scratch_base(char **out) {
 // The loss partial count of a fused SDDMM; with nnz == 0 the loss is 0.
 static nsd_status finish_loss(const SddmmParams &p, double *loss, hipStream_t st) {
     // with nnz == 0 there are no partials and the finaliser writes 0
-    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k, sddmm_vec_ok(p)).nblocks, loss, st);
+    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k).nblocks, loss, st);
 }
 
 }  // namespace nsd
@@ -430,7 +419,7 @@ nsd_status nsd_loss_sum_spmv(const nsd_csr *A, const nsd_csc *At, const float *x
     }
     LossJob job;
     job.p1 = w.loss_part;
-    job.n1 = sddmm_shape(A->nnz, 1, true).nblocks;
+    job.n1 = sddmm_shape(A->nnz, 1).nblocks;
     job.loss = loss;
     return vec1_reduce(cols, job, st);
 }
@@ -448,7 +437,7 @@ nsd_status nsd_loss_frob_spmm(const nsd_csr *A, const nsd_csc *At, const float *
     ComputeWs w;
     NSD_TRY(carve_compute(ws, ws_bytes, A, At, k, &w));
     hipStream_t st = as_stream(stream);
-    if (A->nnz > 0 && frob_fused_ok(k, B, C, dB)) {
+    if (A->nnz > 0 && k > 1 && k <= kMaxFusedWidth) {
         // row pass (C and the loss), long-row combine, one column pass (dB
         // and dA, with B_j the column's own row), long-column combine, total
         FrobParams f;
@@ -516,7 +505,7 @@ nsd_status nsd_spmm_vjp(const nsd_csr *A, const nsd_csc *At, const float *X, con
         // one pass over the columns: own row X_j, gathered row G_i (NULL:
         // ones): dA[p] = <G_i, X_j>, dX = A^T G; no loss
         DualPass pass = col_dual(A, At, G, X, k, 1.f, dX, w.part_col, dA, 1.f, false);
-        if (col_dual_ok(pass)) {
+        if (k <= kMaxFusedWidth) {
             NSD_TRY(csc_order_before(A, At, w.valT, w.gradT, w.staging, pass, st));
             NSD_TRY(col_dual_run(A, pass, w.loss_part, nullptr, st));
             return csc_order_after(At, w.valT, w.gradT, w.staging, dA, st);
@@ -566,11 +555,10 @@ nsd_status nsd_loss_mf(const nsd_csr *A, const nsd_csc *At, const float *valT, c
     NSD_REQUIRE(A->nrows == 0 || dU != nullptr, "dU is NULL");
     NSD_REQUIRE(A->ncols == 0 || dV != nullptr, "dV is NULL");
     NSD_REQUIRE(A->nnz == 0 || (U && V), "U/V is NULL");
-    const bool vec = k % 4 == 0 && aligned16(U) && aligned16(V) && aligned16(dU) && aligned16(dV);
     ComputeWs w;
     NSD_TRY(carve_compute(ws, ws_bytes, A, At, k, &w));
     hipStream_t st = as_stream(stream);
-    if (!dual_supported(k, vec)) {
+    if (k > kMaxFusedWidth) {
         // wider than a fused slot: r_ij once (CSR order) with the loss,
         // then dU over the rows and dV over the columns with r as weights
         ResidParams r;
@@ -584,14 +572,14 @@ nsd_status nsd_loss_mf(const nsd_csr *A, const nsd_csc *At, const float *valT, c
         r.x = A->val;
         r.rbuf = w.rbuf;
         r.part = w.loss_part;
-        NSD_TRY(resid_pass(r, vec, st));
+        NSD_TRY(resid_pass(r, st));
         SgrParams rows = rows_params(A, V, k, -2.f * seed, dU, w.part);
         rows.w = w.rbuf;
         NSD_TRY(segreduce(rows, st));
         SgrParams cols = cols_params(A, At, U, k, -2.f * seed, dV, w.part_col);
         cols.w = w.rbuf;  // through At->perm
         NSD_TRY(segreduce(cols, st));
-        return loss_finalize(w.loss_part, resid_blocks(A->nnz, k, vec), loss, st);
+        return loss_finalize(w.loss_part, resid_blocks(A->nnz, k), loss, st);
     }
     // row pass: dU = -2 seed sum_j r_ij V_j with the loss; column pass:
     // dV = -2 seed sum_i r_ij U_i, r recomputed; both in one launch
@@ -631,8 +619,8 @@ static nsd_status check_coo3(const nsd_coo3 *X) {
     return NSD_OK;
 }
 
-// Per-mode chunk partials, the loss partials, and (ranks above 64, which a
-// fused slot may not hold) the residual of every stored entry.
+// Per-mode chunk partials, the loss partials, and (ranks that a fused slot
+// does not hold) the residual of every stored entry.
 static size_t cp_ws_bytes(const nsd_coo3 *X, int rank) {
     size_t b = 0;
     nsd_plan plans[3];
@@ -640,12 +628,10 @@ static size_t cp_ws_bytes(const nsd_coo3 *X, int rank) {
         b += round256(sgr_part_bytes(X->mode[n].plan, std::max(rank, 1)));
         plans[n] = X->mode[n].plan;
     }
-    int64_t blocks = std::max(cp_blocks(plans, rank, true), cp_blocks(plans, rank, false));
-    if (rank > 64)
-        blocks = std::max({blocks, resid_blocks(X->nnz, rank, true),
-                           resid_blocks(X->nnz, rank, false)});
+    int64_t blocks = cp_blocks(plans, rank);
+    if (rank > kMaxFusedWidth) blocks = std::max(blocks, resid_blocks(X->nnz, rank));
     b += round256(std::max<int64_t>(blocks, 1) * sizeof(double));
-    if (rank > 64) b += round256((size_t)std::max(X->nnz, 1) * sizeof(float));
+    if (rank > kMaxFusedWidth) b += round256((size_t)std::max(X->nnz, 1) * sizeof(float));
     return b;
 }
 
@@ -653,7 +639,7 @@ static size_t cp_ws_bytes(const nsd_coo3 *X, int rank) {
 // 0's order (written to dX and, unscaled, to a buffer in X's input order),
 // then one mode pass per mode reading it through the mode's permutation.
 static nsd_status cp_wide(const nsd_coo3 *X, const float *const *F, int rank, float seed,
-                          double *loss, float *dX, float *const *dF, bool vec, char *b,
+                          double *loss, float *dX, float *const *dF, char *b,
                           hipStream_t st) {
     float *part[3];
     for (int n = 0; n < 3; ++n) {
@@ -662,9 +648,7 @@ static nsd_status cp_wide(const nsd_coo3 *X, const float *const *F, int rank, fl
     }
     double *loss_part = reinterpret_cast<double *>(b);
     nsd_plan plans[3] = {X->mode[0].plan, X->mode[1].plan, X->mode[2].plan};
-    const int64_t blocks = std::max({cp_blocks(plans, rank, true), cp_blocks(plans, rank, false),
-                                     resid_blocks(X->nnz, rank, true),
-                                     resid_blocks(X->nnz, rank, false)});
+    const int64_t blocks = std::max(cp_blocks(plans, rank), resid_blocks(X->nnz, rank));
     b += round256(std::max<int64_t>(blocks, 1) * sizeof(double));
     float *rbuf = reinterpret_cast<float *>(b);
     const nsd_coo3_mode &m0 = X->mode[0];
@@ -683,7 +667,7 @@ static nsd_status cp_wide(const nsd_coo3 *X, const float *const *F, int rank, fl
     r.seed = seed;
     r.lscale = 0.5;
     r.part = loss_part;
-    NSD_TRY(resid_pass(r, vec, st));
+    NSD_TRY(resid_pass(r, st));
     for (int n = 0; n < 3; ++n) {
         const nsd_coo3_mode &md = X->mode[n];
         MttkrpParams m;
@@ -703,9 +687,9 @@ static nsd_status cp_wide(const nsd_coo3 *X, const float *const *F, int rank, fl
         m.other[1] = md.idx_b;
         m.fac[0] = F[(n + 1) % 3];
         m.fac[1] = F[(n + 2) % 3];
-        NSD_TRY(mttkrp_pass(m, 3, vec, st));
+        NSD_TRY(mttkrp_pass(m, 3, st));
     }
-    return loss_finalize(loss_part, resid_blocks(X->nnz, rank, vec), loss, st);
+    return loss_finalize(loss_part, resid_blocks(X->nnz, rank), loss, st);
 }
 
 nsd_status nsd_cp_workspace_size(const nsd_coo3 *X, int32_t rank, size_t *bytes) {
@@ -729,14 +713,12 @@ nsd_status nsd_loss_cp(const nsd_coo3 *X, const float *F1, const float *F2, cons
         NSD_REQUIRE(X->nnz == 0 || F[n] != nullptr, "F%d is NULL", n + 1);
     }
     NSD_REQUIRE(X->nnz == 0 || dX != nullptr, "dX is NULL");
-    bool vec = rank % 4 == 0;
-    for (int n = 0; n < 3; ++n) vec = vec && aligned16(F[n]) && aligned16(dF[n]);
     const size_t need = cp_ws_bytes(X, rank);
     if (ws == nullptr || ws_bytes < need)
         return fail(NSD_ERR_WORKSPACE, "workspace %zu bytes at %p, need %zu", ws_bytes, ws, need);
     char *b = static_cast<char *>(ws);
-    if (vec ? rank > 256 : rank > 64) return cp_wide(X, F, rank, seed, loss, dX, dF, vec, b,
-                                                     as_stream(stream));
+    if (rank > kMaxFusedWidth)
+        return cp_wide(X, F, rank, seed, loss, dX, dF, b, as_stream(stream));
     CpParams f;
     for (int n = 0; n < 3; ++n) {
         const nsd_coo3_mode &md = X->mode[n];
@@ -762,7 +744,7 @@ nsd_status nsd_loss_cp(const nsd_coo3 *X, const float *F1, const float *F2, cons
         m.seed = seed;
     }
     f.loss_part = reinterpret_cast<double *>(b);
-    return cp_fused(f, vec, loss, as_stream(stream));
+    return cp_fused(f, loss, as_stream(stream));
 }
 
 }  // extern "C"

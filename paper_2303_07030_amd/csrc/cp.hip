@@ -23,11 +23,11 @@
 namespace nsd {
 
 // State of one slot walking one work item of a mode pass.
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 struct CpSlot {
     const CpMode &m;
     int64_t s, k, b0;
-    int lane, g, col;
+    int lane, g, col, dup;
     bool on, first_mode;
     int row;
     bool carry;     // the open segment started before this item (a later chunk)
@@ -38,10 +38,12 @@ struct CpSlot {
 
     __device__ __forceinline__ CpSlot(const CpMode &m_, int64_t s_, int lane_, bool fm,
                                       double &ls)
-        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), col((lane_ % G) * VEC),
-          first_mode(fm), lsum(ls) {
+        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), first_mode(fm), lsum(ls) {
         const SgrParams &a = m.s;
-        on = col < a.k;  // rank <= G * VEC
+        const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // rank <= G * VEC
+        col = lc.col;
+        dup = lc.dup;
+        on = lc.on;
         const int64_t a0 = a.plan.item_ptr[s];
         b0 = a.plan.item_ptr[s + 1];
         row = a.segidx[a0];
@@ -73,8 +75,8 @@ struct CpSlot {
 #pragma unroll
         for (int u = 0; u < U; ++u) same = same && r[u] == row;
         // Every load of the batch is issued before any of them is used: the
-        // addresses are always valid (a lane past the rank reads column 0 and
-        // its data is dropped), so no load sits in a branch that must wait.
+        // addresses are always valid (a lane past the rank reads column 0
+        // and its data is dropped), so no load sits in a branch that must wait.
         const int cl = on ? col : 0;
         Vec<VEC> t[U], fb[U], ow[U];
 #pragma unroll
@@ -93,7 +95,8 @@ struct CpSlot {
         }
         float d[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) d[u] = (same || !on) ? ownv.dot(t[u]) : ow[u].dot(t[u]);
+        for (int u = 0; u < U; ++u)
+            d[u] = (same || !on) ? lane_dot<RAG>(ownv, t[u], dup) : lane_dot<RAG>(ow[u], t[u], dup);
         float res[U];
         if constexpr (G == 1) {
 #pragma unroll
@@ -137,11 +140,11 @@ struct CpSlot {
 // the entries' metadata in tiles of G (lane g loads entry g of a tile, each
 // batch takes its fields by broadcast); narrow slots load them per entry.
 // The next tile's (batch's) metadata is in flight under the current one.
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ int cp_walk(const CpMode &m, int64_t s, int lane, bool first_mode,
                                        double &lsum, Vec<VEC> &part_acc) {
     const SgrParams &a = m.s;
-    CpSlot<VEC, G, U> st(m, s, lane, first_mode, lsum);
+    CpSlot<VEC, G, U, RAG> st(m, s, lane, first_mode, lsum);
     const int64_t a0 = a.plan.item_ptr[s], b0 = st.b0;
     // Fields of entry q; past the item they are those of its last entry
     // (every load unconditional, so none is consumed before its batch); the
@@ -206,22 +209,21 @@ __device__ __forceinline__ int cp_walk(const CpMode &m, int64_t s, int lane, boo
     return st.pend ? st.row : -1;  // a chunk partial, stored by store_chunk_partial
 }
 
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void cp_block(const CpMode &m, int b, bool first_mode, double &lsum) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
-    const int g = threadIdx.x % G;
+    const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
     if (b < m.item_blocks) {
         const int64_t s = (int64_t)b * kSlots + threadIdx.x / G;
         Vec<VEC> pacc;
         pacc.zero();
         int pseg = -1;
-        if (s < m.s.plan.nitems) pseg = cp_walk<VEC, G, U>(m, s, lane, first_mode, lsum, pacc);
-        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, g * VEC,
-                                    g * VEC < m.s.k);
+        if (s < m.s.plan.nitems) pseg = cp_walk<VEC, G, U, RAG>(m, s, lane, first_mode, lsum, pacc);
+        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, col,
+                                    on);
     } else {
-        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, g * VEC,
-                          g * VEC < m.s.k);
+        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
     }
 }
 
@@ -232,14 +234,14 @@ __device__ __forceinline__ void cp_block(const CpMode &m, int b, bool first_mode
 #define NSD_CP_OCCUPANCY
 #endif
 
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) NSD_CP_OCCUPANCY void cp_kernel(CpParams f) {
     const int b0 = f.m[0].item_blocks + f.m[0].empty_blocks;
     const int b1 = b0 + f.m[1].item_blocks + f.m[1].empty_blocks;
     double lsum = 0.0;
-    if ((int)blockIdx.x < b0) cp_block<VEC, G, U>(f.m[0], blockIdx.x, true, lsum);
-    else if ((int)blockIdx.x < b1) cp_block<VEC, G, U>(f.m[1], blockIdx.x - b0, false, lsum);
-    else cp_block<VEC, G, U>(f.m[2], blockIdx.x - b1, false, lsum);
+    if ((int)blockIdx.x < b0) cp_block<VEC, G, U, RAG>(f.m[0], blockIdx.x, true, lsum);
+    else if ((int)blockIdx.x < b1) cp_block<VEC, G, U, RAG>(f.m[1], blockIdx.x - b0, false, lsum);
+    else cp_block<VEC, G, U, RAG>(f.m[2], blockIdx.x - b1, false, lsum);
     const double t = block_sum(lsum);
     if (threadIdx.x == 0) f.loss_part[blockIdx.x] = t;
 }
@@ -254,15 +256,15 @@ constexpr int cp_unroll() {
 #endif
 }
 
-int64_t cp_blocks(const nsd_plan *plans, int rank, bool vec) {
-    const WidthPlan wp = width_plan(rank, vec);
+int64_t cp_blocks(const nsd_plan *plans, int rank) {
+    const WidthPlan wp = width_plan(rank);
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < 3; ++i) n += ceil_div(plans[i].nitems, slots) + ceil_div(plans[i].nempty, slots);
     return n;
 }
 
-template <int VEC, int G>
+template <int VEC, int G, bool RAG>
 static nsd_status launch_cp(CpParams f, double *loss, hipStream_t st) {
     constexpr int kSlots = kBlock / G;
     int grid = 0;
@@ -274,7 +276,7 @@ static nsd_status launch_cp(CpParams f, double *loss, hipStream_t st) {
     }
     if (grid == 0) return loss_finalize(f.loss_part, 0, loss, st);
     probe_begin(NSD_KERNEL_CP, st);
-    cp_kernel<VEC, G, cp_unroll<G>()><<<grid, kBlock, 0, st>>>(f);
+    cp_kernel<VEC, G, cp_unroll<G>(), RAG><<<grid, kBlock, 0, st>>>(f);
     probe_end(NSD_KERNEL_CP, st);
     NSD_TRY(check_launch("cp_kernel"));
     // the loss total rides on the last combine launch
@@ -292,13 +294,13 @@ struct CpLauncher {
     CpParams f;
     double *loss;
     hipStream_t st;
-    template <int VEC, int G>
-    nsd_status operator()() { return launch_cp<VEC, G>(f, loss, st); }
+    template <int VEC, int G, bool RAG>
+    nsd_status operator()() { return launch_cp<VEC, G, RAG>(f, loss, st); }
 };
 
-nsd_status cp_fused(CpParams f, bool vec, double *loss, hipStream_t st) {
+nsd_status cp_fused(CpParams f, double *loss, hipStream_t st) {
     CpLauncher fn{f, loss, st};
-    return dispatch_width(width_plan(f.m[0].s.k, vec), fn);
+    return dispatch_width(width_plan(f.m[0].s.k), fn);
 }
 
 }  // namespace nsd

@@ -45,11 +45,11 @@ struct CpnParams {
     double *loss_part = nullptr;
 };
 
-template <int N, int VEC, int G, int U>
+template <int N, int VEC, int G, int U, bool RAG>
 struct CpnSlot {
     const CpnMode<N> &m;
     int64_t s, k, b0;
-    int lane, g, col;
+    int lane, g, col, dup;
     bool on, first_mode;
     int row;
     bool carry;
@@ -59,10 +59,12 @@ struct CpnSlot {
 
     __device__ __forceinline__ CpnSlot(const CpnMode<N> &m_, int64_t s_, int lane_, bool fm,
                                        double &ls)
-        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), col((lane_ % G) * VEC),
-          first_mode(fm), lsum(ls) {
+        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), first_mode(fm), lsum(ls) {
         const SgrParams &a = m.s;
-        on = col < a.k;
+        const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // rank <= G * VEC
+        col = lc.col;
+        dup = lc.dup;
+        on = lc.on;
         const int64_t a0 = a.plan.item_ptr[s];
         b0 = a.plan.item_ptr[s + 1];
         row = a.segidx[a0];
@@ -115,7 +117,8 @@ struct CpnSlot {
         }
         float d[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) d[u] = (same || !on) ? ownv.dot(t[u]) : ow[u].dot(t[u]);
+        for (int u = 0; u < U; ++u)
+            d[u] = (same || !on) ? lane_dot<RAG>(ownv, t[u], dup) : lane_dot<RAG>(ow[u], t[u], dup);
         float res[U];
         if constexpr (G == 1) {
 #pragma unroll
@@ -164,11 +167,11 @@ struct CpnSlot {
 // which is sum R (fac0 o t') regrouped by fiber.  The open fiber keeps its
 // factor row fv and the partial product pv = own o fv, so an entry in it
 // needs N - 2 gathers and one dot product.
-template <int N, int VEC, int G, int U>
+template <int N, int VEC, int G, int U, bool RAG>
 struct CpnFiberSlot {
     const CpnMode<N> &m;
     int64_t s, k, b0;
-    int lane, g, col;
+    int lane, g, col, dup;
     bool on, first_mode;
     int row;
     bool carry;
@@ -179,10 +182,12 @@ struct CpnFiberSlot {
 
     __device__ __forceinline__ CpnFiberSlot(const CpnMode<N> &m_, int64_t s_, int lane_, bool fm,
                                             double &ls)
-        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), col((lane_ % G) * VEC),
-          first_mode(fm), lsum(ls) {
+        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), first_mode(fm), lsum(ls) {
         const SgrParams &a = m.s;
-        on = col < a.k;
+        const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // rank <= G * VEC
+        col = lc.col;
+        dup = lc.dup;
+        on = lc.on;
         const int64_t a0 = a.plan.item_ptr[s];
         b0 = a.plan.item_ptr[s + 1];
         row = a.segidx[a0];
@@ -252,7 +257,7 @@ struct CpnFiberSlot {
         float d[U];
         if (samef) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) d[u] = pv.dot(t[u]);
+            for (int u = 0; u < U; ++u) d[u] = lane_dot<RAG>(pv, t[u], dup);
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -260,7 +265,7 @@ struct CpnFiberSlot {
                 Vec<VEC> q;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) q.v[e] = o.v[e] * fr[u].v[e];
-                d[u] = q.dot(t[u]);
+                d[u] = lane_dot<RAG>(q, t[u], dup);
             }
         }
         float res[U];
@@ -396,12 +401,12 @@ __device__ __forceinline__ int cpn_walk(const CpnMode<N> &m, int64_t s, int lane
     return st.pend ? st.row : -1;  // a chunk partial, stored by store_chunk_partial
 }
 
-template <int N, int VEC, int G, int U>
+template <int N, int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void cpn_block(const CpnMode<N> &m, int b, bool first_mode,
                                           double &lsum) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
-    const int g = threadIdx.x % G;
+    const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
     if (b < m.item_blocks) {
         const int64_t s = (int64_t)b * kSlots + threadIdx.x / G;
         Vec<VEC> pacc;
@@ -409,37 +414,36 @@ __device__ __forceinline__ void cpn_block(const CpnMode<N> &m, int b, bool first
         int pseg = -1;
         if (s < m.s.plan.nitems) {
             if (m.fiber)
-                pseg = cpn_walk<N, VEC, G, U, CpnFiberSlot<N, VEC, G, U>>(m, s, lane, first_mode,
+                pseg = cpn_walk<N, VEC, G, U, CpnFiberSlot<N, VEC, G, U, RAG>>(m, s, lane, first_mode,
                                                                           lsum, pacc);
             else
-                pseg = cpn_walk<N, VEC, G, U, CpnSlot<N, VEC, G, U>>(m, s, lane, first_mode, lsum,
+                pseg = cpn_walk<N, VEC, G, U, CpnSlot<N, VEC, G, U, RAG>>(m, s, lane, first_mode, lsum,
                                                                      pacc);
         }
-        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, g * VEC,
-                                    g * VEC < m.s.k);
+        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, col,
+                                    on);
     } else {
-        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, g * VEC,
-                          g * VEC < m.s.k);
+        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
     }
 }
 
 // Block b belongs to the first mode whose block range holds it (modes in
 // order; compile-time mode indices keep the kernel arguments addressed
 // statically).
-template <int M, int N, int VEC, int G, int U>
+template <int M, int N, int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void cpn_dispatch(const CpnParams<N> &f, int b, double &lsum) {
     const int nb = f.m[M].item_blocks + f.m[M].empty_blocks;
     if (b < nb) {
-        cpn_block<N, VEC, G, U>(f.m[M], b, M == 0, lsum);
+        cpn_block<N, VEC, G, U, RAG>(f.m[M], b, M == 0, lsum);
     } else if constexpr (M + 1 < N) {
-        cpn_dispatch<M + 1, N, VEC, G, U>(f, b - nb, lsum);
+        cpn_dispatch<M + 1, N, VEC, G, U, RAG>(f, b - nb, lsum);
     }
 }
 
-template <int N, int VEC, int G, int U>
+template <int N, int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) void cpn_kernel(CpnParams<N> f) {
     double lsum = 0.0;
-    cpn_dispatch<0, N, VEC, G, U>(f, blockIdx.x, lsum);
+    cpn_dispatch<0, N, VEC, G, U, RAG>(f, blockIdx.x, lsum);
     const double t = block_sum(lsum);
     if (threadIdx.x == 0) f.loss_part[blockIdx.x] = t;
 }
@@ -453,7 +457,7 @@ constexpr int cpn_unroll() {
 #endif
 }
 
-template <int N, int VEC, int G>
+template <int N, int VEC, int G, bool RAG>
 static nsd_status launch_cpn(CpnParams<N> f, double *loss, hipStream_t st) {
     constexpr int kSlots = kBlock / G;
     int grid = 0;
@@ -465,7 +469,7 @@ static nsd_status launch_cpn(CpnParams<N> f, double *loss, hipStream_t st) {
     }
     if (grid == 0) return loss_finalize(f.loss_part, 0, loss, st);
     probe_begin(NSD_KERNEL_CPN, st);
-    cpn_kernel<N, VEC, G, cpn_unroll<G>()><<<grid, kBlock, 0, st>>>(f);
+    cpn_kernel<N, VEC, G, cpn_unroll<G>(), RAG><<<grid, kBlock, 0, st>>>(f);
     probe_end(NSD_KERNEL_CPN, st);
     NSD_TRY(check_launch("cpn_kernel"));
     LossJob job;
@@ -483,12 +487,12 @@ struct CpnLauncher {
     CpnParams<N> f;
     double *loss;
     hipStream_t st;
-    template <int VEC, int G>
-    nsd_status operator()() { return launch_cpn<N, VEC, G>(f, loss, st); }
+    template <int VEC, int G, bool RAG>
+    nsd_status operator()() { return launch_cpn<N, VEC, G, RAG>(f, loss, st); }
 };
 
-static int64_t cpn_blocks(const nsd_coon *X, int rank, bool vec) {
-    const WidthPlan wp = width_plan(rank, vec);
+static int64_t cpn_blocks(const nsd_coon *X, int rank) {
+    const WidthPlan wp = width_plan(rank);
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < X->order; ++i)
@@ -498,23 +502,21 @@ static int64_t cpn_blocks(const nsd_coon *X, int rank, bool vec) {
 
 static size_t rnd256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// Loss partials of either form (ranks above 64, which a fused slot may not
-// hold, form the residual once in its own pass).
+// Loss partials of either form (ranks that a fused slot does not hold form
+// the residual once in its own pass).
 static int64_t cpn_loss_parts(const nsd_coon *X, int rank) {
-    int64_t blocks = std::max(cpn_blocks(X, rank, true), cpn_blocks(X, rank, false));
-    if (rank > 64)
-        blocks = std::max({blocks, resid_blocks(X->nnz, rank, true),
-                           resid_blocks(X->nnz, rank, false)});
+    int64_t blocks = cpn_blocks(X, rank);
+    if (rank > kMaxFusedWidth) blocks = std::max(blocks, resid_blocks(X->nnz, rank));
     return std::max<int64_t>(blocks, 1);
 }
 
-// Per-mode chunk partials, the loss partials and, for ranks above 64, the
-// residual of every stored entry.
+// Per-mode chunk partials, the loss partials and, for ranks wider than a
+// fused slot, the residual of every stored entry.
 static size_t cpn_ws_bytes(const nsd_coon *X, int rank) {
     size_t b = 0;
     for (int n = 0; n < X->order; ++n) b += rnd256(sgr_part_bytes(X->mode[n].plan, rank));
     b += rnd256(cpn_loss_parts(X, rank) * sizeof(double));
-    if (rank > 64) b += rnd256((size_t)std::max(X->nnz, 1) * sizeof(float));
+    if (rank > kMaxFusedWidth) b += rnd256((size_t)std::max(X->nnz, 1) * sizeof(float));
     return b;
 }
 
@@ -522,7 +524,7 @@ static size_t cpn_ws_bytes(const nsd_coon *X, int rank) {
 // 0's order (to dX and, unscaled, to a buffer in X's input order), then one
 // mode pass per mode reading it through the mode's permutation.
 static nsd_status cpn_wide(const nsd_coon *X, const float *const *F, int32_t rank, float seed,
-                           double *loss, float *dX, float *const *dF, bool vec, char *b,
+                           double *loss, float *dX, float *const *dF, char *b,
                            hipStream_t st) {
     const int N = X->order;
     float *part[NSD_MAX_ORDER];
@@ -548,7 +550,7 @@ static nsd_status cpn_wide(const nsd_coon *X, const float *const *F, int32_t ran
     r.seed = seed;
     r.lscale = 0.5;
     r.part = loss_part;
-    NSD_TRY(resid_pass(r, vec, st));
+    NSD_TRY(resid_pass(r, st));
     for (int n = 0; n < N; ++n) {
         const nsd_coon_mode &md = X->mode[n];
         MttkrpParams m;
@@ -568,9 +570,9 @@ static nsd_status cpn_wide(const nsd_coon *X, const float *const *F, int32_t ran
             m.other[o] = md.idx[o];
             m.fac[o] = F[(n + 1 + o) % N];
         }
-        NSD_TRY(mttkrp_pass(m, N, vec, st));
+        NSD_TRY(mttkrp_pass(m, N, st));
     }
-    return loss_finalize(loss_part, resid_blocks(X->nnz, rank, vec), loss, st);
+    return loss_finalize(loss_part, resid_blocks(X->nnz, rank), loss, st);
 }
 
 static nsd_status check_coon(const nsd_coon *X) {
@@ -597,7 +599,7 @@ static nsd_status check_coon(const nsd_coon *X) {
 
 template <int N>
 static nsd_status cpn_run(const nsd_coon *X, const float *const *F, int32_t rank, float seed,
-                          double *loss, float *dX, float *const *dF, bool vec, char *b,
+                          double *loss, float *dX, float *const *dF, char *b,
                           hipStream_t st) {
     CpnParams<N> f;
     for (int n = 0; n < N; ++n) {
@@ -635,7 +637,7 @@ static nsd_status cpn_run(const nsd_coon *X, const float *const *F, int32_t rank
     }
     f.loss_part = reinterpret_cast<double *>(b);
     CpnLauncher<N> fn{f, loss, st};
-    return dispatch_width(width_plan(rank, vec), fn);
+    return dispatch_width(width_plan(rank), fn);
 }
 
 }  // namespace nsd
@@ -659,11 +661,9 @@ nsd_status nsd_loss_cpn(const nsd_coon *X, const float *const *F, int32_t rank, 
     NSD_REQUIRE(rank >= 1, "rank = %d < 1", rank);
     NSD_REQUIRE(loss != nullptr && F != nullptr && dF != nullptr, "loss/F/dF is NULL");
     const int N = X->order;
-    bool vec = rank % 4 == 0;
     for (int n = 0; n < N; ++n) {
         NSD_REQUIRE(X->dims[n] == 0 || dF[n] != nullptr, "dF%d is NULL", n + 1);
         NSD_REQUIRE(X->nnz == 0 || F[n] != nullptr, "F%d is NULL", n + 1);
-        vec = vec && aligned16(F[n]) && aligned16(dF[n]);
     }
     NSD_REQUIRE(X->nnz == 0 || dX != nullptr, "dX is NULL");
     const size_t need = cpn_ws_bytes(X, rank);
@@ -671,12 +671,12 @@ nsd_status nsd_loss_cpn(const nsd_coon *X, const float *const *F, int32_t rank, 
         return fail(NSD_ERR_WORKSPACE, "workspace %zu bytes at %p, need %zu", ws_bytes, ws, need);
     char *b = static_cast<char *>(ws);
     hipStream_t st = as_stream(stream);
-    if (vec ? rank > 256 : rank > 64) return cpn_wide(X, F, rank, seed, loss, dX, dF, vec, b, st);
+    if (rank > kMaxFusedWidth) return cpn_wide(X, F, rank, seed, loss, dX, dF, b, st);
     switch (N) {
-        case 3: return cpn_run<3>(X, F, rank, seed, loss, dX, dF, vec, b, st);
-        case 4: return cpn_run<4>(X, F, rank, seed, loss, dX, dF, vec, b, st);
-        case 5: return cpn_run<5>(X, F, rank, seed, loss, dX, dF, vec, b, st);
-        default: return cpn_run<6>(X, F, rank, seed, loss, dX, dF, vec, b, st);
+        case 3: return cpn_run<3>(X, F, rank, seed, loss, dX, dF, b, st);
+        case 4: return cpn_run<4>(X, F, rank, seed, loss, dX, dF, b, st);
+        case 5: return cpn_run<5>(X, F, rank, seed, loss, dX, dF, b, st);
+        default: return cpn_run<6>(X, F, rank, seed, loss, dX, dF, b, st);
     }
 }
 

@@ -34,11 +34,11 @@ namespace nsd {
 
 // State of one slot walking one work item: the open segment, its sum, and
 // the per-batch arithmetic shared by both ways of fetching entry metadata.
-template <int KIND, int VEC, int G, int U>
+template <int KIND, int VEC, int G, int U, bool RAG>
 struct DualSlot {
     const DualPass &m;
     int64_t s, k, b0;
-    int lane, g, col;
+    int lane, g, col, dup;
     bool on;
     int row;
     bool carry;    // the open segment started before this item (a later chunk)
@@ -59,9 +59,12 @@ struct DualSlot {
 #endif
 
     __device__ __forceinline__ DualSlot(const DualPass &m_, int64_t s_, int lane_, double &ls)
-        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), col((lane_ % G) * VEC), lsum(ls) {
+        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), lsum(ls) {
         const SgrParams &a = m.s;
-        on = col < a.k;  // k <= G * VEC on this path
+        const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // k <= G * VEC on this path
+        col = lc.col;
+        dup = lc.dup;
+        on = lc.on;
         const int64_t a0 = a.plan.item_ptr[s];
         b0 = a.plan.item_ptr[s + 1];
         row = a.segidx[a0];
@@ -113,13 +116,13 @@ struct DualSlot {
                 if (!on) {
                     d[u] = 0.f;
                 } else if (r[u] == row) {
-                    d[u] = ownv.dot(xv[u]);
+                    d[u] = lane_dot<RAG>(ownv, xv[u], dup);
                 } else if (r[u] == r[U - 1]) {
-                    d[u] = ownn.dot(xv[u]);
+                    d[u] = lane_dot<RAG>(ownn, xv[u], dup);
                 } else {
                     Vec<VEC> o;
                     o.load(m.own + (int64_t)r[u] * k + col);
-                    d[u] = o.dot(xv[u]);
+                    d[u] = lane_dot<RAG>(o, xv[u], dup);
                 }
             }
             ownv = ownn;  // own row of the last entry's segment
@@ -129,7 +132,7 @@ struct DualSlot {
                 Vec<VEC> o;
                 if (on) o.load(m.own + (int64_t)r[u] * k + col);
                 else o.zero();
-                d[u] = o.dot(xv[u]);
+                d[u] = lane_dot<RAG>(o, xv[u], dup);
             }
         }
         float coef[U];
@@ -188,32 +191,31 @@ struct DualSlot {
 
 // Walks item s; returns the segment of the chunk partial left in `part_acc`
 // (stored with store_chunk_partial), or -1.
-template <int KIND, int VEC, int G, int U>
+template <int KIND, int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ int dual_walk(const DualPass &m, int64_t s, int lane, double &lsum,
                                          Vec<VEC> &part_acc) {
-    DualSlot<KIND, VEC, G, U> st(m, s, lane, lsum);
+    DualSlot<KIND, VEC, G, U, RAG> st(m, s, lane, lsum);
     walk_item<G, U>(m.s, m.s.plan.item_ptr[s], st.b0, st.g, st);
     st.finish();
     part_acc = st.acc;
     return st.pend ? st.row : -1;
 }
 
-template <int KIND, int VEC, int G, int U>
+template <int KIND, int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void dual_block(const DualPass &m, int b, double &lsum) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
-    const int g = threadIdx.x % G;
+    const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
     if (b < m.item_blocks) {
         const int64_t s = (int64_t)b * kSlots + threadIdx.x / G;
         Vec<VEC> pacc;
         pacc.zero();
         int pseg = -1;
-        if (s < m.s.plan.nitems) pseg = dual_walk<KIND, VEC, G, U>(m, s, lane, lsum, pacc);
-        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, g * VEC,
-                                    g * VEC < m.s.k);
+        if (s < m.s.plan.nitems) pseg = dual_walk<KIND, VEC, G, U, RAG>(m, s, lane, lsum, pacc);
+        store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, col,
+                                    on);
     } else {
-        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, g * VEC,
-                          g * VEC < m.s.k);
+        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
     }
 }
 
@@ -224,7 +226,7 @@ __device__ __forceinline__ void dual_block(const DualPass &m, int b, double &lsu
 #define NSD_DUAL_OCCUPANCY
 #endif
 
-template <int KIND, int VEC, int G, int U>
+template <int KIND, int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) NSD_DUAL_OCCUPANCY void dual_kernel(DualParams f) {
     if (f.early.loss && blockIdx.x == gridDim.x - 1) {
         loss_total_block<4>(f.early);  // a few thousand row partials; keeps VGPRs low
@@ -232,8 +234,8 @@ __global__ __launch_bounds__(kBlock) NSD_DUAL_OCCUPANCY void dual_kernel(DualPar
     }
     const int first = f.pass[0].item_blocks + f.pass[0].empty_blocks;
     double lsum = 0.0;
-    if ((int)blockIdx.x < first) dual_block<KIND, VEC, G, U>(f.pass[0], blockIdx.x, lsum);
-    else dual_block<KIND, VEC, G, U>(f.pass[1], (int)blockIdx.x - first, lsum);
+    if ((int)blockIdx.x < first) dual_block<KIND, VEC, G, U, RAG>(f.pass[0], blockIdx.x, lsum);
+    else dual_block<KIND, VEC, G, U, RAG>(f.pass[1], (int)blockIdx.x - first, lsum);
     if (f.loss_part) {
         const double t = block_sum(lsum);
         if (threadIdx.x == 0) f.loss_part[blockIdx.x] = f.loss_beta * t;
@@ -253,8 +255,8 @@ constexpr int dual_unroll() {
 #endif
 }
 
-int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k, bool vec) {
-    const WidthPlan wp = width_plan(k, vec);
+int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k) {
+    const WidthPlan wp = width_plan(k);
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < npass; ++i)
@@ -264,7 +266,7 @@ int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k, bool vec) {
     return n;
 }
 
-template <int KIND, int VEC, int G>
+template <int KIND, int VEC, int G, bool RAG>
 static nsd_status launch_dual(DualParams f, int probe_id, LossJob job, hipStream_t st) {
     constexpr int kSlots = kBlock / G;
     int64_t grid = 0;
@@ -286,7 +288,7 @@ static nsd_status launch_dual(DualParams f, int probe_id, LossJob job, hipStream
     const int64_t launch = grid + (f.early.loss ? 1 : 0);
     if (launch > 0) {
         probe_begin(probe_id, st);
-        dual_kernel<KIND, VEC, G, dual_unroll<G>()><<<(unsigned)launch, kBlock, 0, st>>>(f);
+        dual_kernel<KIND, VEC, G, dual_unroll<G>(), RAG><<<(unsigned)launch, kBlock, 0, st>>>(f);
         probe_end(probe_id, st);
         NSD_TRY(check_launch("dual_kernel"));
     }
@@ -302,25 +304,13 @@ struct DualLauncher {
     int probe_id;
     LossJob job;
     hipStream_t st;
-    template <int VEC, int G>
-    nsd_status operator()() { return launch_dual<KIND, VEC, G>(f, probe_id, job, st); }
+    template <int VEC, int G, bool RAG>
+    nsd_status operator()() { return launch_dual<KIND, VEC, G, RAG>(f, probe_id, job, st); }
 };
 
-bool dual_vec_ok(const DualParams &f) {
-    bool ok = f.pass[0].s.k % 4 == 0;
-    for (int i = 0; i < f.npass; ++i) {
-        const DualPass &m = f.pass[i];
-        ok = ok && aligned16(m.own) && aligned16(m.s.out) && (!m.s.X || aligned16(m.s.X));
-    }
-    return ok;
-}
-
-bool dual_supported(int k, bool vec) { return vec ? k <= 256 : k <= 64; }
-
 nsd_status dual_fused(int kind, DualParams f, int probe_id, LossJob job, hipStream_t st) {
-    const bool vec = dual_vec_ok(f);
-    const WidthPlan wp = width_plan(f.pass[0].s.k, vec);
-    if (!dual_supported(f.pass[0].s.k, vec))
+    const WidthPlan wp = width_plan(f.pass[0].s.k);
+    if (f.pass[0].s.k > kMaxFusedWidth)
         return fail(NSD_ERR_UNSUPPORTED, "dense width k = %d on a fused pass", f.pass[0].s.k);
     if (kind == kDualMf) {
         DualLauncher<kDualMf> fn{f, probe_id, job, st};

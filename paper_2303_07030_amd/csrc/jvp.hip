@@ -116,8 +116,7 @@ template <int MB, int VEC, int G, int U>
 __global__ __launch_bounds__(kBlock) void jvp_kernel(JvpParams<MB> f) {
     constexpr int kSlots = kBlock / G;
     const int g = threadIdx.x % G;
-    const int col = blockIdx.y * (G * VEC) + g * VEC;
-    const bool on = col < f.c.k;
+    const auto [col, dup, on] = lane_cols<VEC>(g, blockIdx.y * (G * VEC), f.c.k);
     if ((int)blockIdx.x >= f.c.item_blocks) {
         const int64_t e = (int64_t)(blockIdx.x - f.c.item_blocks) * kSlots + threadIdx.x / G;
         if (f.primal) zero_segment<VEC>(f.c, e, col, on);
@@ -187,7 +186,7 @@ template <int MB>
 struct JvpLauncher {
     JvpParams<MB> f;
     hipStream_t st;
-    template <int VEC, int G>
+    template <int VEC, int G, bool RAG>
     nsd_status operator()() { return launch_jvp<MB, VEC, G>(f, st); }
 };
 
@@ -259,9 +258,8 @@ nsd_status nsd_spmm_jvp(const nsd_csr *A, const float *dAval, const float *B, co
         NSD_TRY(segreduce(f.c, st));
         return segreduce(f.d[0], st);
     }
-    const bool vec = k % 4 == 0 && aligned16(B) && aligned16(dB) && aligned16(C) && aligned16(dC);
     JvpLauncher<1> fn{f, st};
-    return dispatch_width(width_plan(k, vec), fn);
+    return dispatch_width(width_plan(k), fn);
 }
 
 nsd_status nsd_spmm_jvp_batch_workspace_size(const nsd_csr *A, int32_t k, size_t *bytes) {
@@ -286,8 +284,6 @@ nsd_status nsd_spmm_jvp_batch(const nsd_csr *A, int32_t m, const float *dAval, c
                     need);
     char *w = static_cast<char *>(ws);
     const int64_t nnz = A->nnz, xstride = (int64_t)A->ncols * k, ostride = (int64_t)A->nrows * k;
-    const bool vec0 = k % 4 == 0 && aligned16(B) && (dB == nullptr || aligned16(dB)) &&
-                      (C == nullptr || aligned16(C)) && (dC == nullptr || aligned16(dC));
     // groups of tangents, C with the first (or alone when m == 0)
     for (int32_t t0 = 0; t0 < m || (t0 == 0 && C != nullptr); t0 += kJvpGroup) {
         JvpParams<kJvpGroup> f;
@@ -309,7 +305,7 @@ nsd_status nsd_spmm_jvp_batch(const nsd_csr *A, int32_t m, const float *dAval, c
             continue;
         }
         JvpLauncher<kJvpGroup> fn{f, st};
-        NSD_TRY(dispatch_width(width_plan(k, vec0), fn));
+        NSD_TRY(dispatch_width(width_plan(k), fn));
     }
     return NSD_OK;
 }

@@ -66,8 +66,6 @@ struct Carver {
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 // --------------------------------------------------- device utilities
 
 __device__ __forceinline__ float shfl_xor(float v, int m) { return __shfl_xor(v, m, kWave); }
@@ -100,33 +98,37 @@ __device__ __forceinline__ float lane_xor(float v) {
 template <int VEC>
 struct Vec;
 
+// Four consecutive columns of a dense row, moved in one 16-byte access that
+// needs the alignment of a float only (global memory takes dword-aligned
+// accesses of any size), so rows of every width go through it.
+typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
+
 template <>
 struct Vec<4> {
     float v[4];
     __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0.f; }
     __device__ __forceinline__ void ones() { v[0] = v[1] = v[2] = v[3] = 1.f; }
     __device__ __forceinline__ void load(const float *p) {
-        const float4 t = *reinterpret_cast<const float4 *>(p);
+        const f32x4 t = *reinterpret_cast<const f32x4 *>(p);
         v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
     __device__ __forceinline__ void store(float *p) const {
-        *reinterpret_cast<float4 *>(p) = make_float4(v[0], v[1], v[2], v[3]);
+        const f32x4 t = {v[0], v[1], v[2], v[3]};
+        *reinterpret_cast<f32x4 *>(p) = t;
     }
     // Streamed data, read or written once (a segment's own row, its output
     // row): non-temporal, so that it displaces less of what the L2 holds
     // for reuse (the gathered rows).
     __device__ __forceinline__ void load_nt(const float *p) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 t = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
+        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
         v[0] = t.x;
         v[1] = t.y;
         v[2] = t.z;
         v[3] = t.w;
     }
     __device__ __forceinline__ void store_nt(float *p) const {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const f4 t = {v[0], v[1], v[2], v[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<f4 *>(p));
+        const f32x4 t = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(t, reinterpret_cast<f32x4 *>(p));
     }
     __device__ __forceinline__ void fma(float w, const Vec &x) {
 #pragma unroll
@@ -167,25 +169,24 @@ struct Vec<1> {
 // ----------------------------------------------------- kernel launchers
 
 // Dense width k -> (VEC, G): VEC fp32 per lane, G lanes per dense row chunk.
+// Rows of four columns and more take four per lane, whatever the width and
+// the alignment: in a width that is no multiple of four the last lane steps
+// back to the row's last four columns (lane_cols).
 struct WidthPlan {
-    int vec;   // 4 or 1
+    int vec;   // 4, or 1 below four columns
     int g;     // lanes per row chunk, power of two, <= 64
     int chunk; // columns covered by one chunk = vec * g
+    bool ragged;  // the last lane steps back (k no multiple of vec)
 };
 
-inline WidthPlan width_plan(int k, bool vec_ok) {
+inline WidthPlan width_plan(int k) {
     WidthPlan p;
-    if (k % 4 == 0 && vec_ok) {
-        p.vec = 4;
-        int lanes = k / 4;
-        p.g = 1;
-        while (p.g < lanes && p.g < 64) p.g <<= 1;
-    } else {
-        p.vec = 1;
-        p.g = 1;
-        while (p.g < k && p.g < 64) p.g <<= 1;
-    }
+    p.vec = k >= 4 ? 4 : 1;
+    const int64_t lanes = ceil_div(k, p.vec);
+    p.g = 1;
+    while (p.g < lanes && p.g < 64) p.g <<= 1;
     p.chunk = p.vec * p.g;
+    p.ragged = k % p.vec != 0;
     return p;
 }
 

@@ -35,8 +35,7 @@ template <int VEC, int G, int U>
 __global__ __launch_bounds__(kBlock) void sgr_main_kernel(SgrParams a) {
     constexpr int kSlots = kBlock / G;
     const int g = threadIdx.x % G;
-    const int col = blockIdx.y * (G * VEC) + g * VEC;
-    const bool on = col < a.k;
+    const auto [col, dup, on] = lane_cols<VEC>(g, blockIdx.y * (G * VEC), a.k);
     if ((int)blockIdx.x >= a.item_blocks) {
         zero_segment<VEC>(a, (int64_t)(blockIdx.x - a.item_blocks) * kSlots + threadIdx.x / G,
                           col, on);
@@ -80,7 +79,7 @@ static nsd_status launch_sgr_vg(SgrParams a, hipStream_t st) {
 struct SgrLauncher {
     SgrParams a;
     hipStream_t st;
-    template <int VEC, int G>
+    template <int VEC, int G, bool RAG>
     nsd_status operator()() { return launch_sgr_vg<VEC, G>(a, st); }
 };
 
@@ -91,17 +90,15 @@ nsd_status segreduce(SgrParams a, hipStream_t st) {
         return check_launch("fill_zero_kernel");
     }
     if (a.k == 1) return vec1_reduce(a, LossJob{}, st);
-    // float4 lanes need 16-byte aligned dense rows; otherwise use scalar lanes
-    const WidthPlan wp = width_plan(a.k, aligned16(a.out) && (!a.X || aligned16(a.X)));
     SgrLauncher f{a, st};
-    return dispatch_width(wp, f);
+    return dispatch_width(width_plan(a.k), f);
 }
 
 // ------------------------------------------------------------------ SDDMM
 
 // SDDMM of entries [a0, b0) by one slot:
 //   out[p] = alpha * <X[rowidx[p]], Y[colind[p]]>, lsum += w[p] * <...>.
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void sddmm_range(const SddmmParams &a, int64_t a0, int64_t b0,
                                             int lane, double &lsum) {
     const int g = lane % G;
@@ -123,8 +120,8 @@ __device__ __forceinline__ void sddmm_range(const SddmmParams &a, int64_t a0, in
 #pragma unroll
         for (int u = 0; u < U; ++u) part[u] = 0.f;
         for (int c0 = 0; c0 < a.k; c0 += G * VEC) {
-            const int col = c0 + g * VEC;
-            if (col < a.k) {
+            const auto [col, dup, on] = lane_cols<VEC, RAG>(g, c0, a.k);
+            if (on) {
                 Vec<VEC> xv[U], yv[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -133,7 +130,7 @@ __device__ __forceinline__ void sddmm_range(const SddmmParams &a, int64_t a0, in
                     yv[u].load(a.Y + (int64_t)cc[u] * k + col);
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u) part[u] += xv[u].dot(yv[u]);
+                for (int u = 0; u < U; ++u) part[u] += lane_dot<RAG>(xv[u], yv[u], dup);
             }
         }
         if constexpr (G == 1) {
@@ -162,7 +159,7 @@ __device__ __forceinline__ void sddmm_range(const SddmmParams &a, int64_t a0, in
 }
 
 // Slots over equal entry ranges (nnz-split): no segment structure needed.
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmParams a) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
@@ -170,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmParams a) {
     double lsum = 0.0;
     if (s < a.nslots) {
         const int64_t a0 = s * a.L;
-        sddmm_range<VEC, G, U>(a, a0, min(a0 + (int64_t)a.L, (int64_t)a.nnz), lane, lsum);
+        sddmm_range<VEC, G, U, RAG>(a, a0, min(a0 + (int64_t)a.L, (int64_t)a.nnz), lane, lsum);
     }
     if (a.part) {
         const double t = block_sum(lsum);
@@ -186,9 +183,9 @@ int choose_slot_len(int64_t nnz, int slots_per_wave) {
     return L;
 }
 
-SddmmShape sddmm_shape(int64_t nnz, int k, bool vec_ok) {
+SddmmShape sddmm_shape(int64_t nnz, int k) {
     SddmmShape sh;
-    sh.wp = width_plan(k, vec_ok);
+    sh.wp = width_plan(k);
     if (k == 1) {  // entry by entry (vec1.hip): a slot is a thread's entries
         sh.L = kVec1SddmmEntries;
         sh.nslots = ceil_div(nnz, sh.L);
@@ -202,23 +199,21 @@ SddmmShape sddmm_shape(int64_t nnz, int k, bool vec_ok) {
     return sh;
 }
 
-bool sddmm_vec_ok(const SddmmParams &a) { return (!a.X || aligned16(a.X)) && aligned16(a.Y); }
-
 struct SddmmLauncher {
     SddmmParams a;
     int64_t nb;
     hipStream_t st;
-    template <int VEC, int G>
+    template <int VEC, int G, bool RAG>
     nsd_status operator()() {
         probe_begin(NSD_KERNEL_SDDMM, st);
-        sddmm_kernel<VEC, G, sddmm_unroll<G>()><<<(unsigned)nb, kBlock, 0, st>>>(a);
+        sddmm_kernel<VEC, G, sddmm_unroll<G>(), RAG><<<(unsigned)nb, kBlock, 0, st>>>(a);
         probe_end(NSD_KERNEL_SDDMM, st);
         return check_launch("sddmm_kernel");
     }
 };
 
 nsd_status sddmm(SddmmParams a, hipStream_t st) {
-    const SddmmShape sh = sddmm_shape(a.nnz, a.k, sddmm_vec_ok(a));
+    const SddmmShape sh = sddmm_shape(a.nnz, a.k);
     a.L = sh.L;
     a.nslots = (int32_t)sh.nslots;
     if (sh.nblocks == 0) return NSD_OK;
@@ -329,13 +324,14 @@ nsd_status loss_finalize(const double *part, int64_t n, double *loss, hipStream_
 #define NSD_FROB_OCCUPANCY
 #endif
 
-template <int VEC, int G, int U>
+template <int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) NSD_FROB_OCCUPANCY void frob_row_kernel(FrobParams f) {
     constexpr int kSlots = kBlock / G;
     const SgrParams &a = f.rows;
     const int g = threadIdx.x % G;
-    const int col = g * VEC;  // k <= G * VEC on this path
-    const bool on = col < a.k;
+    const auto lc = lane_cols<VEC, RAG>(g, 0, a.k);  // k <= G * VEC on this path
+    const int col = lc.col, dup = lc.dup;
+    const bool on = lc.on;
     double lsq = 0.0;
     if ((int)blockIdx.x >= a.item_blocks) {
         zero_segment<VEC>(a, (int64_t)(blockIdx.x - a.item_blocks) * kSlots + threadIdx.x / G, col,
@@ -349,7 +345,8 @@ __global__ __launch_bounds__(kBlock) NSD_FROB_OCCUPANCY void frob_row_kernel(Fro
             pseg = sgr_walk<VEC, G, U>(a, s, col, on, [&](int, const Vec<VEC> &c) {
                 if (on)
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) lsq += (double)c.v[e] * c.v[e];
+                    for (int e = 0; e < VEC; ++e)
+                        if (e >= dup) lsq += (double)c.v[e] * c.v[e];
             }, pacc);
         }
         store_chunk_partial<VEC, G>(pseg, pacc, a.part, a.plan.chunk_ord, s, a.k, col, on);
@@ -362,7 +359,7 @@ __global__ __launch_bounds__(kBlock) NSD_FROB_OCCUPANCY void frob_row_kernel(Fro
 // then dB and dA in one linear dual pass over the columns (own row B_j,
 // gathered row C_i) with the loss total in one extra block, then the
 // long-column combine when there are long columns.
-template <int VEC, int G>
+template <int VEC, int G, bool RAG>
 static nsd_status launch_frob(FrobParams f, hipStream_t st) {
     constexpr int kSlots = kBlock / G;
     constexpr int U = sgr_unroll<G>();
@@ -370,7 +367,7 @@ static nsd_status launch_frob(FrobParams f, hipStream_t st) {
     f.rows.chunk_stride = chunk_group<G>();
     const int row_blocks = f.rows.item_blocks + (int)ceil_div(f.rows.plan.nempty, kSlots);
     probe_begin(NSD_KERNEL_FROB_ROW, st);
-    frob_row_kernel<VEC, G, U><<<row_blocks, kBlock, 0, st>>>(f);
+    frob_row_kernel<VEC, G, U, RAG><<<row_blocks, kBlock, 0, st>>>(f);
     probe_end(NSD_KERNEL_FROB_ROW, st);
     NSD_TRY(check_launch("frob_row_kernel"));
     NSD_TRY((launch_fix<VEC, G>(f.rows, f.seg_loss, 0.5, st)));
@@ -388,25 +385,21 @@ static nsd_status launch_frob(FrobParams f, hipStream_t st) {
 }
 
 int64_t frob_row_blocks(const nsd_plan &rows, int k) {
-    const WidthPlan wp = width_plan(k, true);
+    const WidthPlan wp = width_plan(k);
     const int slots = kBlock / wp.g;
     return ceil_div(rows.nitems, slots) + ceil_div(rows.nempty, slots);
-}
-
-bool frob_fused_ok(int k, const void *B, const void *C, const void *dB) {
-    return k <= 256 && k % 4 == 0 && aligned16(B) && aligned16(C) && aligned16(dB);
 }
 
 struct FrobLauncher {
     FrobParams f;
     hipStream_t st;
-    template <int VEC, int G>
-    nsd_status operator()() { return launch_frob<VEC, G>(f, st); }
+    template <int VEC, int G, bool RAG>
+    nsd_status operator()() { return launch_frob<VEC, G, RAG>(f, st); }
 };
 
 nsd_status frob_fused(FrobParams f, hipStream_t st) {
     FrobLauncher fn{f, st};
-    return dispatch_width(width_plan(f.rows.k, true), fn);
+    return dispatch_width(width_plan(f.rows.k), fn);
 }
 
 }  // namespace nsd

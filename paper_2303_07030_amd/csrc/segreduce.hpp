@@ -91,9 +91,9 @@ struct DualParams {
                                   // run by one extra block (when early.loss is set)
 };
 
-int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k, bool vec);
-bool dual_vec_ok(const DualParams &f);
-bool dual_supported(int k, bool vec);
+int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k);
+// The widths that a slot of one wave holds.
+constexpr int kMaxFusedWidth = 256;
 // Launches the passes and their long-segment combines, the last of which
 // also runs `job` (when job.loss is set); a job without p1 sums the block
 // partials of the dual kernel itself (f.loss_part).
@@ -129,15 +129,13 @@ struct CpParams {
     double *loss_part = nullptr;
 };
 
-int64_t cp_blocks(const nsd_plan *plans, int rank, bool vec);
-nsd_status cp_fused(CpParams f, bool vec, double *loss, hipStream_t st);
+int64_t cp_blocks(const nsd_plan *plans, int rank);
+nsd_status cp_fused(CpParams f, double *loss, hipStream_t st);
 
 int64_t frob_row_blocks(const nsd_plan &rows, int k);
-bool frob_fused_ok(int k, const void *B, const void *C, const void *dB);
 nsd_status frob_fused(FrobParams f, hipStream_t st);
 
-SddmmShape sddmm_shape(int64_t nnz, int k, bool vec_ok);
-bool sddmm_vec_ok(const SddmmParams &a);
+SddmmShape sddmm_shape(int64_t nnz, int k);
 nsd_status sddmm(SddmmParams a, hipStream_t st);
 
 // Width-1 passes (vec1.hip): the gather-reduce (with a loss total of earlier

@@ -16,6 +16,51 @@ constexpr int kBlock = 256;
 constexpr int kBlockWaves = kBlock / kWave;
 constexpr int kHugeChunks = 64;  // matches the plan builder
 
+// ----------------------------------------------------------- lane columns
+
+// The VEC columns of a dense row that lane g of a slot holds, of the chunk
+// that starts at column c0 of k.  A lane whose columns would cross the row's
+// end takes the row's last VEC columns instead: its first `dup` columns are
+// the lane before's too.  Both lanes then hold, add up and store the same
+// values in those columns; only sums over the columns leave them out on the
+// later lane (lane_dot).  RAG says that the width may be no multiple of VEC.
+struct LaneCols {
+    int col, dup;
+    bool on;
+};
+
+template <int VEC, bool RAG = true>
+__device__ __forceinline__ LaneCols lane_cols(int g, int c0, int k) {
+    LaneCols l;
+    l.col = c0 + g * VEC;
+    l.dup = 0;
+    l.on = l.col < k;
+    if constexpr (RAG) {
+        if (l.on) {
+            l.dup = max(l.col + VEC - k, 0);
+            l.col -= l.dup;
+        }
+    }
+    return l;
+}
+
+// <a, b> over the columns that are this lane's own.  Ragged widths are a
+// kernel of their own: with the three selects decided at run time the widths
+// of whole quads lost 3 to 11 % (the GNN layer's pass of k = 256 5.85 -> 6.03
+// ms, the SpMM gradient of k = 64 103 -> 116 us).
+template <bool RAG, int VEC>
+__device__ __forceinline__ float lane_dot(const Vec<VEC> &a, const Vec<VEC> &b, int dup) {
+    if constexpr (VEC == 4 && RAG) {
+        // selects, not factors of 0: the other lane's column may be infinite
+        float s = dup > 0 ? 0.f : a.v[0] * b.v[0];
+        s = dup > 1 ? 0.f : __builtin_fmaf(a.v[1], b.v[1], s);
+        s = dup > 2 ? 0.f : __builtin_fmaf(a.v[2], b.v[2], s);
+        return __builtin_fmaf(a.v[3], b.v[3], s);
+    } else {
+        return a.dot(b);
+    }
+}
+
 // --------------------------------------------------------- entry metadata
 
 // The value held by lane `src` of this lane's slot of G lanes (src uniform
@@ -377,8 +422,7 @@ __device__ __forceinline__ void fix_block(const SgrParams &a, int b, int wave_bl
     if (huge != (n > kHugeChunks)) return;
     double lsq = 0.0;
     for (int c0 = 0; c0 < a.k; c0 += G * VEC) {
-        const int col = c0 + g * VEC;
-        const bool on = col < a.k;
+        const auto [col, dup, on] = lane_cols<VEC>(g, c0, a.k);
         // kFixDepth chunk partials in flight per lane, as many running sums
         Vec<VEC> acc[kFixDepth];
 #pragma unroll
@@ -427,7 +471,8 @@ __device__ __forceinline__ void fix_block(const SgrParams &a, int b, int wave_bl
             acc[0].scale(a.alpha);
             acc[0].store(a.out + (int64_t)seg * k + col);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) lsq += (double)acc[0].v[e] * acc[0].v[e];
+            for (int e = 0; e < VEC; ++e)
+                if (e >= dup) lsq += (double)acc[0].v[e] * acc[0].v[e];
         }
     }
     if (seg_loss) {
@@ -556,28 +601,29 @@ inline nsd_status launch_fix(const SgrParams &a, double *seg_loss, double beta, 
     return launch_fixes<VEC, G>(f, st);
 }
 
-// Calls f.template operator()<VEC, G>() for the lane layout wp.
+// Calls f.template operator()<VEC, G, RAG>() for the lane layout wp.
+template <bool RAG, class F>
+inline nsd_status dispatch_quads(const WidthPlan &wp, F &f) {
+    switch (wp.g) {
+        case 2: return f.template operator()<4, 2, RAG>();
+        case 4: return f.template operator()<4, 4, RAG>();
+        case 8: return f.template operator()<4, 8, RAG>();
+        case 16: return f.template operator()<4, 16, RAG>();
+        case 32: return f.template operator()<4, 32, RAG>();
+        default: return f.template operator()<4, 64, RAG>();
+    }
+}
+
 template <class F>
 inline nsd_status dispatch_width(const WidthPlan &wp, F &f) {
     if (wp.vec == 4) {
-        switch (wp.g) {
-            case 1: return f.template operator()<4, 1>();
-            case 2: return f.template operator()<4, 2>();
-            case 4: return f.template operator()<4, 4>();
-            case 8: return f.template operator()<4, 8>();
-            case 16: return f.template operator()<4, 16>();
-            case 32: return f.template operator()<4, 32>();
-            default: return f.template operator()<4, 64>();
-        }
+        if (wp.g == 1) return f.template operator()<4, 1, false>();  // k = 4
+        return wp.ragged ? dispatch_quads<true>(wp, f) : dispatch_quads<false>(wp, f);
     }
-    switch (wp.g) {
-        case 1: return f.template operator()<1, 1>();
-        case 2: return f.template operator()<1, 2>();
-        case 4: return f.template operator()<1, 4>();
-        case 8: return f.template operator()<1, 8>();
-        case 16: return f.template operator()<1, 16>();
-        case 32: return f.template operator()<1, 32>();
-        default: return f.template operator()<1, 64>();
+    switch (wp.g) {  // fewer than four columns
+        case 1: return f.template operator()<1, 1, false>();
+        case 2: return f.template operator()<1, 2, false>();
+        default: return f.template operator()<1, 4, false>();
     }
 }
 

@@ -1,6 +1,5 @@
 // Wide-rank form of the factorisation and CP losses: any rank, also above
-// what one slot of the fused kernels holds (256 columns with 16-byte aligned
-// rows, 64 otherwise).
+// what one slot of the fused kernels holds (256 columns).
 //
 // The fused kernels recompute an entry's residual in every pass from the
 // dense rows they hold in registers; with more columns than a slot holds,
@@ -54,8 +53,8 @@ __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
 #pragma unroll
             for (int u = 0; u < U; ++u) part[u] = 0.f;
             for (int c0 = 0; c0 < a.k; c0 += G * VEC) {
-                const int col = c0 + g * VEC;
-                if (col < a.k) {
+                const auto [col, dup, on] = lane_cols<VEC>(g, c0, a.k);
+                if (on) {
                     Vec<VEC> t[U];
 #pragma unroll
                     for (int u = 0; u < U; ++u) t[u].load(a.fac[0] + (int64_t)c[u][0] * k + col);
@@ -72,7 +71,7 @@ __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
 #pragma unroll
                     for (int u = 0; u < U; ++u)
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) part[u] += t[u].v[e];
+                        for (int e = 0; e < VEC; ++e) part[u] += e >= dup ? t[u].v[e] : 0.f;
                 }
             }
             // lane g ends with the model value of entry g / (G / U)
@@ -109,16 +108,16 @@ static nsd_status resid_order(ResidParams a, int64_t nblocks, hipStream_t st) {
     }
 }
 
-int64_t resid_blocks(int64_t nnz, int k, bool vec) { return sddmm_shape(nnz, k, vec).nblocks; }
+int64_t resid_blocks(int64_t nnz, int k) { return sddmm_shape(nnz, k).nblocks; }
 
-nsd_status resid_pass(ResidParams a, bool vec, hipStream_t st) {
-    const SddmmShape sh = sddmm_shape(a.nnz, a.k, vec);
+nsd_status resid_pass(ResidParams a, hipStream_t st) {
+    const SddmmShape sh = sddmm_shape(a.nnz, a.k);
     if (sh.nblocks == 0) return NSD_OK;
     if (sh.wp.g != kWave)
         return fail(NSD_ERR_UNSUPPORTED, "residual pass of width %d below one wave", a.k);
     a.L = sh.L;
     a.nslots = (int32_t)sh.nslots;
-    return sh.wp.vec == 4 ? resid_order<4>(a, sh.nblocks, st) : resid_order<1>(a, sh.nblocks, st);
+    return resid_order<4>(a, sh.nblocks, st);
 }
 
 // ------------------------------------------------------ mode gather-reduce
@@ -137,9 +136,9 @@ struct MttkrpSlot {
     bool pend = false;  // acc is a chunk partial of segment `row`, not yet stored
     Vec<VEC> acc;
 
-    __device__ __forceinline__ MttkrpSlot(const MttkrpParams &m_, int64_t a0, int64_t b0_, int col_)
-        : m(m_), k(m_.s.k), b0(b0_), col(col_) {
-        on = col < m.s.k;
+    __device__ __forceinline__ MttkrpSlot(const MttkrpParams &m_, int64_t a0, int64_t b0_, int col_,
+                                          bool on_)
+        : m(m_), k(m_.s.k), b0(b0_), col(col_), on(on_) {
         row = m.s.segidx[a0];
         carry = a0 > 0 && m.s.segidx[a0 - 1] == row;
         acc.zero();
@@ -195,8 +194,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpParams m) {
     constexpr int kSlots = kBlock / G;
     const SgrParams &a = m.s;
     const int g = threadIdx.x % G;
-    const int col = blockIdx.y * (G * VEC) + g * VEC;
-    const bool on = col < a.k;
+    const auto [col, dup, on] = lane_cols<VEC>(g, blockIdx.y * (G * VEC), a.k);
     if ((int)blockIdx.x >= a.item_blocks) {
         zero_segment<VEC>(a, (int64_t)(blockIdx.x - a.item_blocks) * kSlots + threadIdx.x / G,
                           col, on);
@@ -208,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpParams m) {
     int pseg = -1;
     if (s < a.plan.nitems) {
         const int64_t a0 = a.plan.item_ptr[s], b0 = a.plan.item_ptr[s + 1];
-        MttkrpSlot<N, VEC, G, U> st(m, a0, b0, col);
+        MttkrpSlot<N, VEC, G, U> st(m, a0, b0, col, on);
         walk_item<G, U>(a, a0, b0, g, st);
         st.finish();
         pacc = st.acc;
@@ -240,12 +238,12 @@ static nsd_status mttkrp_order(MttkrpParams m, int order, hipStream_t st) {
     }
 }
 
-nsd_status mttkrp_pass(MttkrpParams m, int order, bool vec, hipStream_t st) {
+nsd_status mttkrp_pass(MttkrpParams m, int order, hipStream_t st) {
     if (m.s.nnz == 0) return segreduce(m.s, st);  // zero fill
-    const WidthPlan wp = width_plan(m.s.k, vec);
+    const WidthPlan wp = width_plan(m.s.k);
     if (wp.g != kWave)
         return fail(NSD_ERR_UNSUPPORTED, "mode pass of width %d below one wave", m.s.k);
-    return wp.vec == 4 ? mttkrp_order<4>(m, order, st) : mttkrp_order<1>(m, order, st);
+    return mttkrp_order<4>(m, order, st);
 }
 
 }  // namespace nsd

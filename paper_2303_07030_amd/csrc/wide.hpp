@@ -25,9 +25,9 @@ struct ResidParams {
 };
 
 // Loss partials resid_pass writes (one per block).
-int64_t resid_blocks(int64_t nnz, int k, bool vec);
-// Needs a slot of a whole wave: k > 64, or k > 256 with float4 rows.
-nsd_status resid_pass(ResidParams a, bool vec, hipStream_t st);
+int64_t resid_blocks(int64_t nnz, int k);
+// Needs a slot of a whole wave: k > 128.
+nsd_status resid_pass(ResidParams a, hipStream_t st);
 
 // Mode pass of a CP gradient of an order-`order` tensor from a formed
 // residual: s is the gather-reduce over the mode's plan (segidx = mode
@@ -40,6 +40,6 @@ struct MttkrpParams {
     const float *fac[NSD_MAX_ORDER - 1] = {};
 };
 
-nsd_status mttkrp_pass(MttkrpParams m, int order, bool vec, hipStream_t st);
+nsd_status mttkrp_pass(MttkrpParams m, int order, hipStream_t st);
 
 }  // namespace nsd

@@ -1,0 +1,125 @@
+"""Widths that are no multiple of four: the last lane of a slot steps back to
+the row's last four columns and shares some with the lane before.  Every
+remainder at the narrowest widths, at the edges of each slot size and past a
+wave's chunk, against the fp64 oracle; and a shared column that is infinite.
+"""
+import numpy as np
+import pytest
+import torch
+
+from helpers import assert_mag_close
+from test_gpu_parity import (check_cp, check_cpn, check_frob, dev, edge_pattern, host,
+                             oracle_dok, run_bilinear, run_cp, run_cpn, run_frob)
+from test_gpu_wide import check_mf_all, cp_case, dev_offset, empty_offset, mf_case
+
+pytestmark = pytest.mark.gpu
+
+# 2, 3: below one quad; then lanes * 4 - 3 .. - 1 around the slots of 2 to 64
+WIDTHS = [2, 3, 5, 6, 7, 9, 10, 15, 17, 31, 35, 63, 66, 127, 130, 255]
+
+
+@pytest.fixture(scope="module")
+def nsd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2303_07030_amd import nsd as m
+    return m
+
+
+def operand_of(seed, k):
+    from paper_2303_07030_amd.operand import DeviceCsr
+    pat = edge_pattern(seed)
+    return pat, DeviceCsr(*pat, k_hint=k)
+
+
+@pytest.mark.parametrize("k", WIDTHS)
+def test_matrix_losses(nsd, orc, k):
+    (nrows, ncols, rowptr, colind, val), A = operand_of(31, k)
+    rng = np.random.default_rng(k)
+    H = rng.standard_normal((ncols, k)).astype(np.float32)
+    G = rng.standard_normal((nrows, k)).astype(np.float32)
+    check_frob(orc, nrows, ncols, rowptr, colind, val, H, k, run_frob(nsd, A, H, k, seed=2.0),
+               seed=2.0)
+    Lg, dAg, dHg = run_bilinear(nsd, A, H, G, k, seed=0.25)
+    D = oracle_dok(orc, nrows, ncols, rowptr, colind, val)
+    rows = np.repeat(np.arange(nrows, dtype=np.int32), np.diff(rowptr))
+    L, Lm = orc.loss_bilinear(D, G, H, k)
+    dA, dAm = orc.sddmm(D, G, H, k, rows, colind, alpha=0.25)
+    dH, dHm = orc.spmm_t(D, G, k, alpha=0.25)
+    assert_mag_close(Lg, L, Lm, what="loss")
+    assert_mag_close(dAg, dA, dAm, what="dA")
+    assert_mag_close(dHg, dH, dHm, what="dH")
+    # the sampled product by itself, its rows at odd addresses
+    out = torch.full((A.nnz,), np.nan, dtype=torch.float32, device="cuda")
+    nsd.nsd_sddmm(A.desc, dev_offset(G), dev_offset(H), k, 0.25, out)
+    assert_mag_close(host(out), dA, dAm, what="sddmm")
+
+
+@pytest.mark.parametrize("k", WIDTHS)
+def test_factorisation(nsd, orc, k):
+    from paper_2303_07030_amd.operand import DeviceCsr
+    nrows, ncols, rowptr, colind, val, U, V = mf_case(k)
+    A = DeviceCsr(nrows, ncols, rowptr, colind, val, k_hint=k)
+    loss = torch.empty(1, dtype=torch.float64, device="cuda")
+    dU, dV = empty_offset((nrows, k)), empty_offset((ncols, k))
+    nsd.nsd_loss_mf(A.desc, A.csc, None, dev_offset(U), dev(V), k, 0.5, loss, dU, dV,
+                    A.workspace(k))
+    D = oracle_dok(orc, nrows, ncols, rowptr, colind, val)
+    check_mf_all(orc, D, U, V, k, host(loss)[0], host(dU), host(dV), 0.5)
+
+
+@pytest.mark.parametrize("rank", WIDTHS)
+def test_cp(nsd, orc, rank):
+    from paper_2303_07030_amd.operand import DeviceCoo3, DeviceCooN
+    dims, i, j, l, val, F = cp_case(rank)
+    X = DeviceCoo3(dims, i, j, l, val, rank_hint=rank)
+    check_cp(orc, dims, i, j, l, val, F, rank, run_cp(nsd, X, F, rank, seed=0.75), seed=0.75)
+    # with fibers (two long modes, short others) and without
+    for dims in ((6, 5, 40, 3), (9, 8, 7, 6)):
+        rng = np.random.default_rng(rank)
+        nnz = int(np.prod(dims)) // 2
+        keys = rng.choice(2 * nnz, size=nnz, replace=False)
+        coords = [c.astype(np.int32) for c in np.unravel_index(keys, dims)]
+        val = rng.standard_normal(nnz).astype(np.float32)
+        F = [(0.3 * rng.standard_normal((d, rank))).astype(np.float32) for d in dims]
+        X = DeviceCooN(dims, coords, val, rank_hint=rank, item_len=16)
+        check_cpn(orc, dims, coords, val, F, rank, run_cpn(nsd, X, F, rank, seed=0.5), seed=0.5)
+
+
+@pytest.mark.parametrize("k", WIDTHS + [258, 515])
+def test_tangents(nsd, orc, k):
+    (nrows, ncols, rowptr, colind, val), A = operand_of(33, k)
+    rng = np.random.default_rng(k)
+    m = 5
+    B, dB = (rng.standard_normal(s).astype(np.float32) for s in ((ncols, k), (m, ncols, k)))
+    dval = rng.standard_normal((m, A.nnz)).astype(np.float32)
+    C = torch.full((nrows, k), np.nan, device="cuda")
+    dC = torch.full((m, nrows, k), np.nan, device="cuda")
+    ws = torch.empty(nsd.nsd_spmm_jvp_batch_workspace_size(A.desc, k), dtype=torch.uint8,
+                     device="cuda")
+    nsd.nsd_spmm_jvp_batch(A.desc, m, dev(dval), dev(B), dev(dB), k, C, dC, ws)
+    D = oracle_dok(orc, nrows, ncols, rowptr, colind, val)
+    assert_mag_close(host(C), *orc.spmm(D, B, k), what="C")
+    for t in range(m):
+        Dt = oracle_dok(orc, nrows, ncols, rowptr, colind, dval[t])
+        (r1, m1), (r2, m2) = orc.spmm(Dt, B, k), orc.spmm(D, dB[t], k)
+        assert_mag_close(host(dC[t]), r1 + r2, m1 + m2, what=f"dC[{t}]")
+
+
+@pytest.mark.parametrize("k", [5, 6, 7, 63, 258])
+def test_infinite_shared_column(nsd, k):
+    """Column k - 4 is the last lane's and the lane before's: an infinity
+    there reaches a product once, and stays an infinity of its sign."""
+    from paper_2303_07030_amd.operand import DeviceCsr
+    A = DeviceCsr(2, 2, np.array([0, 1, 2], np.int32), np.array([0, 1], np.int32),
+                  np.ones(2, np.float32), k_hint=k)
+    X, Y = torch.ones((2, k), device="cuda"), torch.ones((2, k), device="cuda")
+    X[0, k - 4] = float("inf")
+    Y[1, k - 4] = float("-inf")
+    out = torch.empty(2, device="cuda")
+    nsd.nsd_sddmm(A.desc, X, Y, k, 1.0, out)
+    assert host(out).tolist() == [np.inf, -np.inf]
+    dA, dY, loss = torch.empty(2, device="cuda"), torch.empty((2, k), device="cuda"), \
+        torch.empty(1, dtype=torch.float64, device="cuda")
+    nsd.nsd_loss_bilinear(A.desc, A.csc, Y, X, k, 1.0, loss, dA, dY, A.workspace(k))
+    assert host(dA).tolist() == [np.inf, -np.inf]
