@@ -13,6 +13,9 @@
 //                        dA = <C_i, B_j> of L = 1/2 ||A B||^2; with O = H,
 //                        X = G it is the whole bilinear layer
 //                        L = sum (A H) o G: dA = <G_i, H_j>, dH = A^T G.
+//                        kDualLinAdd: the same for a later slice of the
+//                        columns of rows wider than a slot, d_p including the
+//                        product over the columns before (sdd[pos_p] so far).
 //   residual (kDualMf):  c_p = r_p = w_p - d_p, loss += r_p^2: the row and
 //                        column passes of sparse matrix factorisation.
 // These are the paper's sums over the stored keys of A with the dense rows
@@ -36,8 +39,9 @@ namespace nsd {
 // the per-batch arithmetic shared by both ways of fetching entry metadata.
 template <int KIND, int VEC, int G, int U, bool RAG>
 struct DualSlot {
+    static constexpr bool kLongBatch = true;
     const DualPass &m;
-    int64_t s, k, b0;
+    int64_t s, k, b0;  // k: the stride of the dense rows
     int lane, g, col, dup;
     bool on;
     int row;
@@ -59,7 +63,7 @@ struct DualSlot {
 #endif
 
     __device__ __forceinline__ DualSlot(const DualPass &m_, int64_t s_, int lane_, double &ls)
-        : m(m_), s(s_), k(m_.s.k), lane(lane_), g(lane_ % G), lsum(ls) {
+        : m(m_), s(s_), k(m_.s.stride()), lane(lane_), g(lane_ % G), lsum(ls) {
         const SgrParams &a = m.s;
         const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // k <= G * VEC on this path
         col = lc.col;
@@ -161,10 +165,11 @@ struct DualSlot {
                     }
                 }
             } else {
-                const float tot = transpose_reduce<G, U>(d, lane);
+                float tot = transpose_reduce<G, U>(d, lane);
                 constexpr int kRep = G / U;
                 const int us = g / kRep;  // the entry whose total this lane holds
                 if (g % kRep == 0 && p + us < b0) {
+                    if constexpr (KIND == kDualLinAdd) tot += m.sdd[ps];
                     if (m.sdd) m.sdd[ps] = m.sdd_alpha * tot;
                     if (m.count_loss) lsum += (double)ws * tot;
                 }
@@ -315,6 +320,17 @@ nsd_status dual_fused(int kind, DualParams f, int probe_id, LossJob job, hipStre
     if (kind == kDualMf) {
         DualLauncher<kDualMf> fn{f, probe_id, job, st};
         return dispatch_width(wp, fn);
+    }
+    if (kind == kDualLinAdd) {
+        // slices of wider rows are of 32 or 64 lanes
+        DualLauncher<kDualLinAdd> fn{f, probe_id, job, st};
+        if (wp.g == 32)
+            return wp.ragged ? fn.template operator()<4, 32, true>()
+                             : fn.template operator()<4, 32, false>();
+        if (wp.g == 64)
+            return wp.ragged ? fn.template operator()<4, 64, true>()
+                             : fn.template operator()<4, 64, false>();
+        return fail(NSD_ERR_UNSUPPORTED, "a column slice of width %d", f.pass[0].s.k);
     }
     DualLauncher<kDualLin> fn{f, probe_id, job, st};
     return dispatch_width(wp, fn);

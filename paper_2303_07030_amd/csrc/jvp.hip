@@ -34,6 +34,7 @@ struct JvpParams {
 
 template <int MB, int VEC, int G, int U>
 struct JvpSlot {
+    static constexpr bool kLongBatch = false;
     const JvpParams<MB> &f;
     int64_t s, k, b0;
     int col;

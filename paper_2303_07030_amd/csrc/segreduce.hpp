@@ -16,6 +16,10 @@ struct SgrParams {
     const float *X = nullptr;         // gathered dense operand (NULL: ones)
     float alpha = 1.f;
     float *out = nullptr;             // [nseg x k]
+    // Floats from one row of X, out (and a dual pass's own rows) to the next
+    // where the pass takes k columns of wider rows (dual passes; 0: k)
+    int32_t ld = 0;
+    __host__ __device__ int64_t stride() const { return ld ? ld : k; }
     float *part = nullptr;            // chunk partials (sgr_part_bytes)
     // Rows of `part` that hold a long segment's partials: its first chunk's
     // and, past it, those of the chunks at item indexes divisible by
@@ -67,11 +71,14 @@ struct LossJob {
 // dense row `own` (see dual.hip):
 //   d_p = <own[seg_p], X[idx_p]>,  out[seg] = alpha * sum_p c_p X[idx_p],
 // with c_p = w_p (kDualLin; then sdd[pos_p] = sdd_alpha * d_p when sdd is
-// set, and loss += w_p d_p when count_loss) or c_p = w_p - d_p (kDualMf;
+// set, and loss += w_p d_p when count_loss; kDualLinAdd: the same, where
+// sdd[pos_p] holds the product over the columns before this pass's and d_p
+// includes it there) or c_p = w_p - d_p (kDualMf;
 // loss += c_p^2 when count_loss).  pos_p = wperm[p] when the weights are
 // permuted, else p.
 constexpr int kDualLin = 0;
 constexpr int kDualMf = 1;
+constexpr int kDualLinAdd = 2;
 
 struct DualPass {
     SgrParams s;

@@ -118,19 +118,31 @@ __device__ __forceinline__ void walk_item(const SgrParams &a, int64_t a0, int64_
                 rest(t + G, npos, nr, nc, nw);
                 if (t + 2 * G < b0) ppos = position(t + 2 * G);
             }
-            for (int base = 0; base < G && t + base < b0; base += U) {
-                int r[U], c[U], pos[U];
-                float w[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    r[u] = slot_bcast<G>(tr, base + u);
-                    c[u] = slot_bcast<G>(tc, base + u);
-                    pos[u] = slot_bcast<G>(tpos, base + u);
-                    w[u] = slot_bcast<G>(tw, base + u);
-                }
-                const int src = base + g / (G / U);
-                st.batch(t + base, r, c, pos, w, __shfl(tpos, src, G), __shfl(tw, src, G));
+            // A dual pass's batch is hundreds of instructions; four copies of
+            // it cost the column pass of k = 64 4 % (51.2 -> 53.2 us).  Left to
+            // the compiler otherwise: it makes no copies of full-wave slots'
+            // loop, and told so it ran the GNN layer's pass 2 % slower.  (A
+            // macro: as a lambda the body waits for more loads than it needs.)
+#define NSD_WALK_BATCHES                                                                \
+    for (int base = 0; base < G && t + base < b0; base += U) {                          \
+        int r[U], c[U], pos[U];                                                         \
+        float w[U];                                                                     \
+        _Pragma("unroll") for (int u = 0; u < U; ++u) {                                 \
+            r[u] = slot_bcast<G>(tr, base + u);                                         \
+            c[u] = slot_bcast<G>(tc, base + u);                                         \
+            pos[u] = slot_bcast<G>(tpos, base + u);                                     \
+            w[u] = slot_bcast<G>(tw, base + u);                                         \
+        }                                                                               \
+        const int src = base + g / (G / U);                                             \
+        st.batch(t + base, r, c, pos, w, __shfl(tpos, src, G), __shfl(tw, src, G));     \
+    }
+            if constexpr (Slot::kLongBatch && G < 64) {
+#pragma clang loop unroll(disable)
+                NSD_WALK_BATCHES
+            } else {
+                NSD_WALK_BATCHES
             }
+#undef NSD_WALK_BATCHES
             tr = nr;
             tc = nc;
             tpos = npos;
@@ -241,6 +253,7 @@ __device__ __forceinline__ void store_chunk_partial(int seg, Vec<VEC> acc, float
 // every segment completed inside the item.
 template <int VEC, int G, int U, class SegDone>
 struct SgrSlot {
+    static constexpr bool kLongBatch = false;
     const SgrParams &a;
     int64_t s, k;
     int col;
@@ -317,7 +330,7 @@ __device__ __forceinline__ void zero_segment(const SgrParams &a, int64_t e, int 
     if (e < a.plan.nempty && on) {
         Vec<VEC> z;
         z.zero();
-        z.store(a.out + (int64_t)a.plan.empty_seg[e] * a.k + col);
+        z.store(a.out + a.plan.empty_seg[e] * a.stride() + col);
     }
 }
 
@@ -469,7 +482,7 @@ __device__ __forceinline__ void fix_block(const SgrParams &a, int b, int wave_bl
         }
         if ((!huge || wave == 0) && q == 0 && on) {
             acc[0].scale(a.alpha);
-            acc[0].store(a.out + (int64_t)seg * k + col);
+            acc[0].store(a.out + seg * a.stride() + col);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 if (e >= dup) lsq += (double)acc[0].v[e] * acc[0].v[e];

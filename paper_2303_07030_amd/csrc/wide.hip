@@ -127,6 +127,7 @@ nsd_status resid_pass(ResidParams a, hipStream_t st) {
 // from the walk, the others are read per batch).
 template <int N, int VEC, int G, int U>
 struct MttkrpSlot {
+    static constexpr bool kLongBatch = false;
     const MttkrpParams &m;
     int64_t k, b0;
     int col;

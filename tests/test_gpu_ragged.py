@@ -123,3 +123,31 @@ def test_infinite_shared_column(nsd, k):
         torch.empty(1, dtype=torch.float64, device="cuda")
     nsd.nsd_loss_bilinear(A.desc, A.csc, Y, X, k, 1.0, loss, dA, dY, A.workspace(k))
     assert host(dA).tolist() == [np.inf, -np.inf]
+
+
+@pytest.mark.parametrize("perm_plans", [False, True])
+@pytest.mark.parametrize("k", [257, 258, 260, 512, 513, 1027])
+def test_column_slices(nsd, orc, k, perm_plans):
+    """Rows wider than a slot: column passes of at most 256 columns that add
+    up the sampled products, in A's order and in CSC order."""
+    from paper_2303_07030_amd.operand import DeviceCsr
+    nrows, ncols, rowptr, colind, val = edge_pattern(35)
+    A = DeviceCsr(nrows, ncols, rowptr, colind, val, k_hint=k, perm_plans=perm_plans)
+    rng = np.random.default_rng(k)
+    X = rng.standard_normal((ncols, k)).astype(np.float32)
+    G = rng.standard_normal((nrows, k)).astype(np.float32)
+    D = oracle_dok(orc, nrows, ncols, rowptr, colind, val)
+    rows = np.repeat(np.arange(nrows, dtype=np.int32), np.diff(rowptr))
+    dA, dAm = orc.sddmm(D, G, X, k, rows, colind)
+    dX, dXm = orc.spmm_t(D, G, k)
+    got, gotX = torch.full((A.nnz,), np.nan, device="cuda"), empty_offset((ncols, k))
+    nsd.nsd_spmm_vjp(A.desc, A.csc, dev_offset(X), dev(G), k, got, gotX, A.workspace(k))
+    assert_mag_close(host(got), dA, dAm, what="vjp dA")
+    assert_mag_close(host(gotX), dX, dXm, what="vjp dX")
+    L, Lm = orc.loss_bilinear(D, G, X, k)
+    Lg, dAg, dHg = run_bilinear(nsd, A, X, G, k, seed=-0.5)
+    assert_mag_close(Lg, L, Lm, what="loss")
+    assert_mag_close(dAg, -0.5 * dA, 0.5 * dAm, what="dA")
+    assert_mag_close(dHg, -0.5 * dX, 0.5 * dXm, what="dH")
+    check_frob(orc, nrows, ncols, rowptr, colind, val, X, k, run_frob(nsd, A, X, k, seed=3.0),
+               seed=3.0)
