@@ -353,6 +353,18 @@ nsd_status nsd_perm_plan_build(int32_t n, const int32_t *perm, int inverse, int3
                                uint16_t *src_local, uint16_t *dst_local, nsd_perm_plan *plan,
                                void *ws, size_t ws_bytes, void *stream);
 
+/*
+ * Both plans of one permutation at once: *plan of dst[q] = src[perm[q]] and
+ * *inv_plan of dst[perm[q]] = src[q], for little more than one of them.  They
+ * share near_local [n] and far_local [n] and have a stage [n] each (caller
+ * arrays).  `ws` and the rest as for nsd_perm_plan_build.  Synchronous.
+ */
+nsd_status nsd_perm_plan_build_pair(int32_t n, const int32_t *perm, int32_t *stage,
+                                    int32_t *inv_stage, uint16_t *near_local,
+                                    uint16_t *far_local, nsd_perm_plan *plan,
+                                    nsd_perm_plan *inv_plan, void *ws, size_t ws_bytes,
+                                    void *stream);
+
 /* The plan's permutation applied to src: an exact fp32 copy in two
  * coalesced passes; staging [n] is caller scratch; src and dst must not
  * alias.  Async. */

@@ -127,6 +127,8 @@ _SIGS = {
     "nsd_perm_plan_workspace_size": (C.c_int, [_I, C.POINTER(_SZ)]),
     "nsd_perm_plan_build": (C.c_int, [_I, _P, C.c_int, _P, _P, _P, C.POINTER(nsd_perm_plan),
                                       _P, _SZ, _P]),
+    "nsd_perm_plan_build_pair": (C.c_int, [_I, _P, _P, _P, _P, _P, C.POINTER(nsd_perm_plan),
+                                           C.POINTER(nsd_perm_plan), _P, _SZ, _P]),
     "nsd_permute_f32": (C.c_int, [C.POINTER(nsd_perm_plan), _P, _P, _P, _P]),
     "nsd_csr_expand_rows": (C.c_int, [_I, _I, _P, _P, _P]),
     "nsd_coo_to_csr": (C.c_int, [_I, _I, _I, _P, _P, _P, C.c_int, _P, _P, _P, _P, _P,
@@ -300,6 +302,18 @@ def nsd_perm_plan_build(n, perm, inverse, stage, src_local, dst_local, ws,
            "nsd_perm_plan_build")
     plan._keep = dict(stage=stage, src_local=src_local, dst_local=dst_local)
     return plan
+
+
+def nsd_perm_plan_build_pair(n, perm, stage, inv_stage, near_local, far_local, ws, stream=None):
+    """(plan of dst[q] = src[perm[q]], plan of dst[perm[q]] = src[q])"""
+    plan, inv = nsd_perm_plan(), nsd_perm_plan()
+    _check(_lib.nsd_perm_plan_build_pair(n, _p(perm), _p(stage), _p(inv_stage), _p(near_local),
+                                         _p(far_local), C.byref(plan), C.byref(inv), _p(ws),
+                                         _nbytes(ws), _stream(stream)),
+           "nsd_perm_plan_build_pair")
+    plan._keep = dict(stage=stage, src_local=far_local, dst_local=near_local)
+    inv._keep = dict(stage=inv_stage, src_local=near_local, dst_local=far_local)
+    return plan, inv
 
 
 def nsd_permute_f32(plan: nsd_perm_plan, src, dst, staging, stream=None):

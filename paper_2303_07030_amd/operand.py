@@ -50,6 +50,15 @@ def build_perm_plan(n, perm, inverse, device, stream=None):
     return nsd.nsd_perm_plan_build(n, perm, inverse, stage, src_local, dst_local, ws, stream)
 
 
+def build_perm_plans(n, perm, device, stream=None):
+    """Two-pass forms of a permutation and of its inverse, from one partition."""
+    stages = [torch.empty(max(n, 1), dtype=torch.int32, device=device) for _ in range(2)]
+    local = [torch.empty(max(n, 1), dtype=torch.uint16, device=device) for _ in range(2)]
+    ws = torch.empty(max(nsd.nsd_perm_plan_workspace_size(n), 256), dtype=torch.uint8,
+                     device=device)
+    return nsd.nsd_perm_plan_build_pair(n, perm, *stages, *local, ws, stream)
+
+
 class DeviceCsr:
     def __init__(self, nrows: int, ncols: int, rowptr, colind, val, device="cuda",
                  build_csc: bool = True, stream=None, k_hint: int = 64, item_len=None,
@@ -95,8 +104,7 @@ class DeviceCsr:
             plans = self.nnz >= PERM_PLAN_MIN_NNZ
         if plans and self.nnz > 0:
             # the descriptor holds copies of the plans; their arrays live here
-            self.to_csc = build_perm_plan(self.nnz, self.perm, 0, dev, stream)
-            self.to_csr = build_perm_plan(self.nnz, self.perm, 1, dev, stream)
+            self.to_csc, self.to_csr = build_perm_plans(self.nnz, self.perm, dev, stream)
             self.csc.to_csc, self.csc.to_csr = self.to_csc, self.to_csr
         return self.csc
 

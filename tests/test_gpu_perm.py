@@ -67,6 +67,23 @@ def test_plan_build_many_windows(nsd, n, kind, inverse):
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("n", [0, 1, 32767, 32769, 300 * 32768 + 77])
+def test_plan_pair_moves_both_ways(nsd, n):
+    """The two plans of one partition, and the same arrays as the plans built
+    one by one."""
+    from paper_2303_07030_amd.operand import build_perm_plan, build_perm_plans
+    perm = torch.from_numpy(np.random.default_rng(n).permutation(n).astype(np.int32)).cuda()
+    src = torch.arange(n, device="cuda", dtype=torch.int32).view(torch.float32)
+    dst, staging = (torch.empty(max(n, 1), device="cuda") for _ in range(2))
+    for inverse, plan in enumerate(build_perm_plans(n, perm, "cuda")):
+        nsd.nsd_permute_f32(plan, src, dst, staging)
+        want = torch.argsort(perm) if inverse else perm
+        assert torch.equal(dst[:n].view(torch.int32), want.int())
+        one = build_perm_plan(n, perm, inverse, "cuda")._keep
+        for name, t in plan._keep.items():
+            assert torch.equal(t[:n].cpu(), one[name][:n].cpu()), name
+
+
 @pytest.mark.parametrize("inverse", [0, 1])
 @pytest.mark.parametrize("where", [(0, 1), (0, 99_999), (40_000, 70_000), (99_998, 99_999)])
 def test_perm_plan_rejects_a_repeated_index(nsd, inverse, where):
