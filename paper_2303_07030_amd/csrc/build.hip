@@ -162,12 +162,22 @@ nsd_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *t
 
 // ------------------------------------------------------------ radix sort
 
-constexpr int kSortThreads = 256;
 constexpr int kSortRounds = 16;  // 64-element rounds per wave
-constexpr int kSortTile = kSortThreads * kSortRounds;
-constexpr int kBins = 256;
-constexpr int kSortWaves = kSortThreads / kWave;
 constexpr int kMaxPayloads = 3;
+
+// A pass sorts by a digit of 8 bits, or of up to 10 where that takes a pass
+// less (digit_bits): a pass moves every key and payload once whatever its
+// digit.  Sorts of kSortStreamMin elements and more take tiles of 8,192 by
+// 512 threads, so that a tile's run of one digit stays near a line; shorter
+// ones 4,096 by 256, enough tiles for all CUs.
+constexpr int kDigitBits = 8, kWideDigitBits = 10;
+
+template <bool NT>
+struct SortShape {
+    static constexpr int kThreads = NT ? 512 : 256;
+    static constexpr int kTile = kThreads * kSortRounds;
+    static constexpr int kWaves = kThreads / kWave;
+};
 
 // A sort's reads of its keys and payloads: non-temporal when the arrays are
 // far larger than the L2s (they are streamed once per pass; the scatter's
@@ -182,15 +192,32 @@ __device__ __forceinline__ int32_t sort_load(const int32_t *p) {
     else return *p;
 }
 
-// The digit of a key at bit `shift`.  A composite key (lo_bits > 0) is the
+static int64_t sort_tiles(int64_t n) {
+    return ceil_div(n, n >= kSortStreamMin ? SortShape<true>::kTile : SortShape<false>::kTile);
+}
+
+// The digit of `bits` bits of a key at bit `shift`.  A composite key (lo_bits > 0) is the
 // pair (hi, lo) read as hi * 2^lo_bits + lo, with lo < 2^lo_bits: sorting by
 // it orders by hi, then by lo, in one sort.
-__device__ __forceinline__ int key_digit(int32_t lo, int32_t hi, int lo_bits, int shift) {
-    const uint32_t l = (uint32_t)lo, h = (uint32_t)hi;
-    // lo_bits and shift are the same for every thread: scalar branches
-    if (lo_bits == 0 || shift + 8 <= lo_bits) return (int)((l >> shift) & (kBins - 1));
-    if (shift >= lo_bits) return (int)((h >> (shift - lo_bits)) & (kBins - 1));
-    return (int)(((l >> shift) | (h << (lo_bits - shift))) & (kBins - 1));  // straddles both
+__device__ __forceinline__ int key_digit(int32_t lo, int32_t hi, int lo_bits, int shift,
+                                         int bits) {
+    const uint32_t l = (uint32_t)lo, h = (uint32_t)hi, mask = (1u << bits) - 1;
+    // lo_bits, shift and bits are the same for every thread: scalar branches
+    if (lo_bits == 0 || shift + bits <= lo_bits) return (int)((l >> shift) & mask);
+    if (shift >= lo_bits) return (int)((h >> (shift - lo_bits)) & mask);
+    return (int)(((l >> shift) | (h << (lo_bits - shift))) & mask);  // straddles both
+}
+
+// Workgroups go to the eight XCDs round-robin (block b on XCD b mod 8), each
+// XCD with its own L2.  This renumbers the blocks so that every XCD takes one
+// contiguous range of the tiles: neighbouring tiles write adjacent runs of
+// one output region, and with the renumbering those runs meet in one L2 and
+// leave it as whole lines instead of partial ones from eight L2s.
+__device__ __forceinline__ int64_t xcd_contiguous_tile() {
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
+    int start = 0;
+    for (int y = 0; y < x; ++y) start += (nb - y + 7) / 8;  // blocks on XCDs before x
+    return start + b / 8;
 }
 
 // Digit counts of one tile.  Keys drawn from a skewed distribution share
@@ -214,18 +241,16 @@ constexpr int kHistPeel = 1;
 // the range check of a builder rides on the read the sort makes anyway.
 // Digits are masked, so such keys stay within the sort's own arrays.
 template <bool PAIR, bool NT>
-__global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const int32_t *keys,
-                                                                  const int32_t *khi,
-                                                                  int lo_bits, int64_t n,
-                                                                  int shift, int64_t ntiles,
-                                                                  int32_t *hist, int32_t *bad,
-                                                                  int32_t max_lo,
-                                                                  int32_t max_hi) {
-    __shared__ int cnt[kBins];
-    cnt[threadIdx.x] = 0;
+__global__ __launch_bounds__(SortShape<NT>::kThreads) void radix_hist_kernel(
+    const int32_t *keys, const int32_t *khi, int lo_bits, int64_t n, int shift, int bits,
+    int64_t ntiles, int32_t *hist, int32_t *bad, int32_t max_lo, int32_t max_hi) {
+    constexpr int kSortThreads = SortShape<NT>::kThreads;
+    __shared__ int cnt[1 << kWideDigitBits];
+    for (int d = threadIdx.x; d < 1 << bits; d += kSortThreads) cnt[d] = 0;
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
+    const int64_t tile = xcd_contiguous_tile();
+    const int64_t base = tile * SortShape<NT>::kTile;
     int key[kSortRounds], hi[kSortRounds];
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
@@ -246,8 +271,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const int32_t 
     for (int i = 0; i < kSortRounds; ++i) {
         const int64_t q = base + (int64_t)i * kSortThreads + threadIdx.x;
         const bool valid = q < n;
-        const int d = PAIR ? key_digit(key[i], hi[i], lo_bits, shift)
-                           : (int)(((uint32_t)key[i] >> shift) & (kBins - 1));
+        const int d = key_digit(key[i], PAIR ? hi[i] : 0, PAIR ? lo_bits : 0, shift, bits);
         uint64_t rest = __ballot(valid);  // lanes not yet counted (wave-uniform)
 #pragma unroll
         for (int it = 0; it < kHistPeel; ++it) {
@@ -261,29 +285,20 @@ __global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const int32_t 
         if ((rest >> lane) & 1) atomicAdd(&cnt[d], 1);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = cnt[threadIdx.x];
-}
-
-// Workgroups go to the eight XCDs round-robin (block b on XCD b mod 8), each
-// XCD with its own L2.  This renumbers the blocks so that every XCD takes one
-// contiguous range of the tiles: neighbouring tiles write adjacent runs of
-// one output region, and with the renumbering those runs meet in one L2 and
-// leave it as whole lines instead of partial ones from eight L2s.
-__device__ __forceinline__ int64_t xcd_contiguous_tile() {
-    const int nb = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
-    int start = 0;
-    for (int y = 0; y < x; ++y) start += (nb - y + 7) / 8;  // blocks on XCDs before x
-    return start + b / 8;
+    for (int d = threadIdx.x; d < 1 << bits; d += kSortThreads)
+        hist[(int64_t)d * ntiles + tile] = cnt[d];
 }
 
 // Stable scatter of one tile.  Wave w owns the tile's elements
 // [w * 1024, (w + 1) * 1024) and walks them in 16 rounds of 64 consecutive
 // elements, so (wave, round, lane) order is input order.  Inside a round the
-// lanes holding the same digit are found with 8 ballots; a lane's rank is the
-// count of such lanes below it plus what earlier rounds of its wave placed.
-// The tile is then staged in LDS in digit order (digit runs in input order)
-// and written back run by run, so consecutive lanes store consecutive
-// addresses of a digit's output range instead of scattering single words.
+// lanes holding the same digit are found with a ballot per digit bit; a
+// lane's rank is the count of such lanes below it plus what earlier rounds of
+// its wave placed.  The keys, then each payload, are staged in LDS in digit
+// order (digit runs in input order) through one buffer and written back run
+// by run, so consecutive lanes store consecutive addresses of a digit's output
+// range instead of scattering single words; every thread keeps the output
+// positions of the slots that it writes.
 // Payloads carried with the keys: in[j] NULL is the element's own index.
 // Carrying what a caller would otherwise gather through the sort's
 // permutation (one random 4-byte read per element) costs 8 more bytes per
@@ -294,25 +309,30 @@ struct SortPayloads {
     int32_t *out[kMaxPayloads];
 };
 
-template <int NP, bool NT>
-__global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
-    const int32_t *kin, SortPayloads pl, int32_t *kout, int64_t n, int lo_bits, int shift,
+template <int NP, bool NT, int BITS>
+__global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kernel(
+    const int32_t *kin, SortPayloads pl, int32_t *kout, int64_t n, int lo_bits, int shift, int bits,
     int64_t ntiles, const int32_t *offs) {
-    __shared__ int wcnt[kSortWaves][kBins];
-    __shared__ int tile_off[kBins];
-    __shared__ int tile_start[kBins];
-    __shared__ int skey[kSortTile];
-    __shared__ int sval[kSortTile];  // one payload at a time
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    constexpr int kThreads = SortShape<NT>::kThreads, kTile = SortShape<NT>::kTile;
+    constexpr int kWaves = SortShape<NT>::kWaves, kBins = 1 << BITS;
+    constexpr int kPer = kBins > kThreads ? kBins / kThreads : 1;  // digits per thread
+    __shared__ uint16_t wcnt[kWaves][kBins];
+    __shared__ uint16_t tile_start[kBins];  // the digit runs' first slots
+    __shared__ int out_base[kBins];         // output position of a digit's slot 0
+    __shared__ uint16_t sdig[kTile];
+    __shared__ int sval[kTile];
+    __shared__ int wave_tot[kWaves];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid / kWave;
     const int64_t tile = xcd_contiguous_tile();
-    for (int w = 0; w < kSortWaves; ++w) wcnt[w][threadIdx.x] = 0;
-    tile_off[threadIdx.x] = offs[(int64_t)threadIdx.x * ntiles + tile];
+    for (int i = tid; i < kWaves * kBins; i += kThreads) (&wcnt[0][0])[i] = 0;
     __syncthreads();
 
-    const int64_t tile0 = tile * kSortTile;
+    const int64_t tile0 = tile * kTile;
     const int64_t base = tile0 + (int64_t)wave * (kSortRounds * kWave);
-    int key[kSortRounds], val[NP][kSortRounds], rank[kSortRounds], dig[kSortRounds];
+    int key[kSortRounds], val[NP][kSortRounds];
+    int rank[kSortRounds];  // digit << 16 | rank in the wave
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
         const int64_t q = base + (int64_t)i * kWave + lane;
@@ -321,80 +341,98 @@ __global__ __launch_bounds__(kSortThreads) void radix_scatter_kernel(
 #pragma unroll
         for (int j = 0; j < NP; ++j)
             val[j][i] = valid ? (pl.in[j] ? sort_load<NT>(pl.in[j] + q) : (int32_t)q) : 0;
-        const int d = key_digit(key[i], val[0][i], lo_bits, shift);
-        dig[i] = d;
+    }
+#pragma unroll
+    for (int i = 0; i < kSortRounds; ++i) {
+        const bool valid = base + (int64_t)i * kWave + lane < n;
+        const int d = key_digit(key[i], val[0][i], lo_bits, shift, bits);
         uint64_t same = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+        for (int b = 0; b < BITS; ++b) {  // bits at or above `bits` are 0 in every lane
             const bool bit = (d >> b) & 1;
             const uint64_t m = __ballot(bit);
             same &= bit ? m : ~m;
         }
         const int below = __popcll(same & __lanemask_lt());
         const int prev = valid ? wcnt[wave][d] : 0;
-        rank[i] = prev + below;
-        if (valid && below == 0) wcnt[wave][d] = prev + __popcll(same);
+        rank[i] = d << 16 | (prev + below);
+        __builtin_amdgcn_wave_barrier();
+        if (valid && below == 0) wcnt[wave][d] = (uint16_t)(prev + __popcll(same));
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // per digit: waves' offsets inside the digit's run, then the run starts
     // (exclusive scan of the digit totals over the tile)
-    int total = 0;
-    {
-        const int d = threadIdx.x;
-        for (int w = 0; w < kSortWaves; ++w) {
-            const int c = wcnt[w][d];
-            wcnt[w][d] = total;
-            total += c;
+    int tot[kPer], sum = 0;
+    const bool mine = tid * kPer < kBins;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        tot[j] = 0;
+        if (mine) {
+            for (int w = 0; w < kWaves; ++w) {
+                const int c = wcnt[w][tid * kPer + j];
+                wcnt[w][tid * kPer + j] = (uint16_t)tot[j];
+                tot[j] += c;
+            }
         }
-        tile_start[d] = total;
+        sum += tot[j];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1) {
+        const int t = __shfl_up(inc, m, kWave);
+        if (lane >= m) inc += t;
+    }
+    if (lane == kWave - 1) wave_tot[wave] = inc;
+    __syncthreads();
+    int start = inc - sum;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+        if (w < wave) start += wave_tot[w];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int d = tid * kPer + j;
+        if (mine) {
+            tile_start[d] = (uint16_t)start;
+            out_base[d] = d < 1 << bits ? offs[(int64_t)d * ntiles + tile] - start : 0;
+        }
+        start += tot[j];
     }
     __syncthreads();
-    for (int off = 1; off < kBins; off <<= 1) {
-        const int add = (int)threadIdx.x >= off ? tile_start[threadIdx.x - off] : 0;
-        __syncthreads();
-        tile_start[threadIdx.x] += add;
-        __syncthreads();
-    }
-    tile_start[threadIdx.x] -= total;  // inclusive -> exclusive
-    __syncthreads();
-    const int tile_n = (int)min<int64_t>(kSortTile, n - tile0);
-    // the keys with the first payload, then each further payload through the
-    // same buffer (the staged keys give every position its output slot): one
-    // buffer keeps four blocks per CU where a buffer per payload allowed two
-    // (measured on MI355X: 0.52 against 0.62 ms per pass of 50M with three
-    // payloads, 0.37 against 0.53 with two).  The staged positions' digits,
-    // found with the first payload (a composite key's high word), serve the
-    // later payloads.
+    const int tile_n = (int)min<int64_t>(kTile, n - tile0);
     int lpos[kSortRounds];  // each element's staging slot (its digit run, its rank)
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
         const int64_t q = base + (int64_t)i * kWave + lane;
-        lpos[i] = q < n ? tile_start[dig[i]] + wcnt[wave][dig[i]] + rank[i] : -1;
+        const int d = rank[i] >> 16;
+        lpos[i] = -1;
+        if (q < n) {
+            lpos[i] = tile_start[d] + wcnt[wave][d] + (rank[i] & 0xffff);
+            sdig[lpos[i]] = (uint16_t)d;
+            sval[lpos[i]] = key[i];
+        }
     }
-    int odig[kSortRounds];
+    __syncthreads();
+    int opos[kSortRounds];
+#pragma unroll
+    for (int r = 0; r < kSortRounds; ++r) {
+        const int lp = tid + r * kThreads;
+        opos[r] = -1;
+        if (lp < tile_n) {
+            opos[r] = out_base[sdig[lp]] + lp;
+            kout[opos[r]] = sval[lp];
+        }
+    }
 #pragma unroll
     for (int j = 0; j < NP; ++j) {
-        if (j > 0) __syncthreads();  // the previous payload is written out
+        __syncthreads();  // the values before are written out
 #pragma unroll
-        for (int i = 0; i < kSortRounds; ++i) {
-            if (lpos[i] >= 0) {
-                if (j == 0) skey[lpos[i]] = key[i];
-                sval[lpos[i]] = val[j][i];
-            }
-        }
+        for (int i = 0; i < kSortRounds; ++i)
+            if (lpos[i] >= 0) sval[lpos[i]] = val[j][i];
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < kSortRounds; ++r) {
-            const int lp = threadIdx.x + r * kSortThreads;
-            if (lp < tile_n) {
-                if (j == 0) odig[r] = key_digit(skey[lp], sval[lp], lo_bits, shift);
-                const int d = odig[r];
-                const int64_t pos = (int64_t)tile_off[d] + (lp - tile_start[d]);
-                if (j == 0) kout[pos] = skey[lp];
-                pl.out[j][pos] = sval[lp];
-            }
-        }
+        for (int r = 0; r < kSortRounds; ++r)
+            if (opos[r] >= 0) pl.out[j][opos[r]] = sval[tid + r * kThreads];
     }
 }
 
@@ -409,47 +447,62 @@ static int key_bits(int32_t max_key) {
     return bits;
 }
 
-static int digit_passes(int bits) { return bits == 0 ? 1 : (bits + 7) / 8; }
+// The digit of a sort by keys of `bits` bits: wide ones where they save a
+// third of the passes (9 to 10 bits, 17 to 20), the bits spread evenly.
+static int digit_bits(int bits) {
+    const int64_t narrow = ceil_div(bits, kDigitBits), wide = ceil_div(bits, kWideDigitBits);
+    return 3 * wide <= 2 * narrow && bits > 0 ? (int)ceil_div(bits, wide) : kDigitBits;
+}
 
 size_t sort_ws_bytes(int64_t n, int32_t max_key, int np) {
     Carver c(nullptr);
-    const int64_t ntiles = ceil_div(n, kSortTile);
+    const int64_t bins = sort_tiles(n) << kWideDigitBits;
     c.take<int32_t>(n);  // ping keys
     c.take<int32_t>(n);  // pong keys
     for (int j = 0; j < np; ++j) {
         c.take<int32_t>(n);  // ping payload j
         c.take<int32_t>(n);  // pong payload j
     }
-    c.take<int32_t>(ntiles * kBins);
-    const size_t scan = scan_ws_bytes(ntiles * kBins);
+    c.take<int32_t>(bins);
+    const size_t scan = scan_ws_bytes(bins);
     (void)max_key;
     return c.bytes() + scan;
 }
 
+template <int NP, bool NT>
+static void launch_scatter_nt(int64_t ntiles, const int32_t *ksrc, const SortPayloads &pl,
+                              int32_t *kdst, int64_t n, int lo_bits, int shift, int bits,
+                              const int32_t *hist, hipStream_t st) {
+    constexpr int T = SortShape<NT>::kThreads;
+    if (bits > kDigitBits)
+        radix_scatter_kernel<NP, NT, kWideDigitBits><<<ntiles, T, 0, st>>>(
+            ksrc, pl, kdst, n, lo_bits, shift, bits, ntiles, hist);
+    else
+        radix_scatter_kernel<NP, NT, kDigitBits><<<ntiles, T, 0, st>>>(
+            ksrc, pl, kdst, n, lo_bits, shift, bits, ntiles, hist);
+}
+
 template <int NP>
 static nsd_status launch_scatter(int64_t ntiles, const int32_t *ksrc, const SortPayloads &pl,
-                                 int32_t *kdst, int64_t n, int lo_bits, int shift,
+                                 int32_t *kdst, int64_t n, int lo_bits, int shift, int bits,
                                  const int32_t *hist, hipStream_t st) {
     if (n >= kSortStreamMin)
-        radix_scatter_kernel<NP, true><<<ntiles, kSortThreads, 0, st>>>(ksrc, pl, kdst, n, lo_bits,
-                                                                        shift, ntiles, hist);
+        launch_scatter_nt<NP, true>(ntiles, ksrc, pl, kdst, n, lo_bits, shift, bits, hist, st);
     else
-        radix_scatter_kernel<NP, false><<<ntiles, kSortThreads, 0, st>>>(ksrc, pl, kdst, n,
-                                                                         lo_bits, shift, ntiles,
-                                                                         hist);
+        launch_scatter_nt<NP, false>(ntiles, ksrc, pl, kdst, n, lo_bits, shift, bits, hist, st);
     return check_launch("radix_scatter_kernel");
 }
 
 template <bool PAIR>
 static void launch_hist(int64_t ntiles, const int32_t *keys, const int32_t *khi, int lo_bits,
-                        int64_t n, int shift, int32_t *hist, int32_t *bad, int32_t max_lo,
-                        int32_t max_hi, hipStream_t st) {
+                        int64_t n, int shift, int bits, int32_t *hist, int32_t *bad,
+                        int32_t max_lo, int32_t max_hi, hipStream_t st) {
     if (n >= kSortStreamMin)
-        radix_hist_kernel<PAIR, true><<<ntiles, kSortThreads, 0, st>>>(
-            keys, khi, lo_bits, n, shift, ntiles, hist, bad, max_lo, max_hi);
+        radix_hist_kernel<PAIR, true><<<ntiles, SortShape<true>::kThreads, 0, st>>>(
+            keys, khi, lo_bits, n, shift, bits, ntiles, hist, bad, max_lo, max_hi);
     else
-        radix_hist_kernel<PAIR, false><<<ntiles, kSortThreads, 0, st>>>(
-            keys, khi, lo_bits, n, shift, ntiles, hist, bad, max_lo, max_hi);
+        radix_hist_kernel<PAIR, false><<<ntiles, SortShape<false>::kThreads, 0, st>>>(
+            keys, khi, lo_bits, n, shift, bits, ntiles, hist, bad, max_lo, max_hi);
 }
 
 // The passes of one sort: keys of `bits` bits, composite when lo_bits > 0
@@ -462,16 +515,17 @@ static nsd_status radix_sort_passes(int64_t n, int bits, int lo_bits, const int3
     if (n <= 0) return NSD_OK;
     if (np < 1 || np > kMaxPayloads) return fail(NSD_ERR_INVALID_ARG, "%d sort payloads", np);
     Carver c(ws);
-    const int64_t ntiles = ceil_div(n, kSortTile);
+    const int64_t ntiles = sort_tiles(n);
     int32_t *kbuf[2] = {c.take<int32_t>(n), c.take<int32_t>(n)};
     int32_t *vbuf[kMaxPayloads][2];
     for (int j = 0; j < np; ++j) {
         vbuf[j][0] = c.take<int32_t>(n);
         vbuf[j][1] = c.take<int32_t>(n);
     }
-    int32_t *hist = c.take<int32_t>(ntiles * kBins);
+    int32_t *hist = c.take<int32_t>(ntiles << kWideDigitBits);
     void *scan_ws = c.base + c.bytes();
-    const int passes = digit_passes(bits);
+    const int db = digit_bits(bits);
+    const int passes = bits == 0 ? 1 : (int)ceil_div(bits, db);
     const int32_t *ksrc = key_in;
     SortPayloads pl{};
     for (int j = 0; j < np; ++j) pl.in[j] = payload_in[j];
@@ -481,18 +535,19 @@ static nsd_status radix_sort_passes(int64_t n, int bits, int lo_bits, const int3
         for (int j = 0; j < np; ++j) pl.out[j] = last ? payload_out[j] : vbuf[j][p & 1];
         int32_t *chk = p == 0 ? bad : nullptr;  // the caller's keys: the first pass reads them
         if (lo_bits > 0)
-            launch_hist<true>(ntiles, ksrc, pl.in[0], lo_bits, n, 8 * p, hist, chk, max_lo, max_hi,
-                              st);
+            launch_hist<true>(ntiles, ksrc, pl.in[0], lo_bits, n, db * p, db, hist, chk, max_lo,
+                              max_hi, st);
         else
-            launch_hist<false>(ntiles, ksrc, nullptr, 0, n, 8 * p, hist, chk, max_lo, max_hi, st);
+            launch_hist<false>(ntiles, ksrc, nullptr, 0, n, db * p, db, hist, chk, max_lo, max_hi,
+                               st);
         NSD_TRY(check_launch("radix_hist_kernel"));
-        NSD_TRY(scan_exclusive(hist, hist, ntiles * kBins, nullptr, scan_ws, st));
+        NSD_TRY(scan_exclusive(hist, hist, ntiles << db, nullptr, scan_ws, st));
         probe_begin(NSD_KERNEL_SORT, st);
-        const int sh = 8 * p;
+        const int sh = db * p;
         switch (np) {
-            case 1: NSD_TRY(launch_scatter<1>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, hist, st)); break;
-            case 2: NSD_TRY(launch_scatter<2>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, hist, st)); break;
-            default: NSD_TRY(launch_scatter<3>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, hist, st));
+            case 1: NSD_TRY(launch_scatter<1>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, db, hist, st)); break;
+            case 2: NSD_TRY(launch_scatter<2>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, db, hist, st)); break;
+            default: NSD_TRY(launch_scatter<3>(ntiles, ksrc, pl, kdst, n, lo_bits, sh, db, hist, st));
         }
         probe_end(NSD_KERNEL_SORT, st);
         ksrc = kdst;
