@@ -596,17 +596,32 @@ static int64_t grid_for(int64_t n) { return ceil_div(n > 0 ? n : 1, kThreads); }
 // starts at the first q whose key is >= r (q = n stands for key nseg).
 constexpr int kSegPer = 4;
 
+// Keys q0 .. q0 + 3, `past` at and past n: one 16-byte load (of dword-aligned
+// words) where all four are there.  With a load per key every instruction of a
+// wave touched sixteen lines for 256 bytes.
+__device__ __forceinline__ void seg_load(const int32_t *key, int64_t q0, int64_t n, int32_t past,
+                                         int32_t (&out)[kSegPer]) {
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+    static_assert(kSegPer == 4, "one 16-byte load");
+    if (q0 + kSegPer <= n) {
+        const i32x4 t = *reinterpret_cast<const i32x4 *>(key + q0);
+#pragma unroll
+        for (int u = 0; u < kSegPer; ++u) out[u] = t[u];
+    } else {
+#pragma unroll
+        for (int u = 0; u < kSegPer; ++u) out[u] = q0 + u < n ? key[q0 + u] : past;
+    }
+}
+
 __global__ void segptr_kernel(int64_t n, int32_t nseg, const int32_t *key, int32_t *segptr) {
     const int64_t q0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * kSegPer;
     if (q0 > n) return;
     // keys outside [0, nseg) (a malformed input) never write out of range
     int32_t prev = q0 == 0 ? -1 : min(key[q0 - 1], nseg);
     int32_t cur[kSegPer];
+    seg_load(key, q0, n, nseg, cur);
 #pragma unroll
-    for (int u = 0; u < kSegPer; ++u) {
-        const int64_t q = q0 + u;
-        cur[u] = q < n ? min(key[q], nseg) : nseg;
-    }
+    for (int u = 0; u < kSegPer; ++u) cur[u] = min(cur[u], nseg);
 #pragma unroll
     for (int u = 0; u < kSegPer; ++u) {
         const int64_t q = q0 + u;
@@ -627,12 +642,10 @@ __global__ void segptr_dups_kernel(int64_t n, int32_t nseg, const int32_t *key,
         int32_t prev = q0 == 0 ? -1 : min(key[q0 - 1], nseg);
         int32_t pcol = q0 == 0 ? -1 : col[q0 - 1];
         int32_t cur[kSegPer], cc[kSegPer];
+        seg_load(key, q0, n, nseg, cur);
+        seg_load(col, q0, n, -1, cc);
 #pragma unroll
-        for (int u = 0; u < kSegPer; ++u) {
-            const int64_t q = q0 + u;
-            cur[u] = q < n ? min(key[q], nseg) : nseg;
-            cc[u] = q < n ? col[q] : -1;
-        }
+        for (int u = 0; u < kSegPer; ++u) cur[u] = min(cur[u], nseg);
 #pragma unroll
         for (int u = 0; u < kSegPer; ++u) {
             const int64_t q = q0 + u;

@@ -118,10 +118,12 @@ __device__ __forceinline__ void walk_item(const SgrParams &a, int64_t a0, int64_
                 rest(t + G, npos, nr, nc, nw);
                 if (t + 2 * G < b0) ppos = position(t + 2 * G);
             }
-            // A dual pass's batch is hundreds of instructions; four copies of
-            // it cost the column pass of k = 64 4 % (51.2 -> 53.2 us).  Left to
-            // the compiler otherwise: it makes no copies of full-wave slots'
-            // loop, and told so it ran the GNN layer's pass 2 % slower.  (A
+            // A dual pass's batch of four entries is hundreds of instructions;
+            // four copies of it cost the column pass of k = 64 4 % (51.2 ->
+            // 53.2 us).  Left to the compiler otherwise: the copies of two
+            // entries' batches that it makes gain 4 % (a GNN layer of k = 32:
+            // 51.8 -> 49.8 us), and of full-wave slots it makes none, but told
+            // so it ran the GNN layer's pass of k = 256 2 % slower.  (A
             // macro: as a lambda the body waits for more loads than it needs.)
 #define NSD_WALK_BATCHES                                                                \
     for (int base = 0; base < G && t + base < b0; base += U) {                          \
@@ -136,7 +138,7 @@ __device__ __forceinline__ void walk_item(const SgrParams &a, int64_t a0, int64_
         const int src = base + g / (G / U);                                             \
         st.batch(t + base, r, c, pos, w, __shfl(tpos, src, G), __shfl(tw, src, G));     \
     }
-            if constexpr (Slot::kLongBatch && G < 64) {
+            if constexpr (Slot::kLongBatch && U >= 4 && G < 64) {
 #pragma clang loop unroll(disable)
                 NSD_WALK_BATCHES
             } else {
