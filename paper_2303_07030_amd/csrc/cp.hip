@@ -213,16 +213,17 @@ template <int VEC, int G, int U, bool RAG>
 __device__ __forceinline__ void cp_block(const CpMode &m, int b, bool first_mode, double &lsum) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
-    const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
     if (b < m.item_blocks) {
         const int64_t s = (int64_t)b * kSlots + threadIdx.x / G;
         Vec<VEC> pacc;
         pacc.zero();
         int pseg = -1;
         if (s < m.s.plan.nitems) pseg = cp_walk<VEC, G, U, RAG>(m, s, lane, first_mode, lsum, pacc);
+        const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
         store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, col,
                                     on);
     } else {
+        const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
         zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
     }
 }

@@ -406,7 +406,6 @@ __device__ __forceinline__ void cpn_block(const CpnMode<N> &m, int b, bool first
                                           double &lsum) {
     constexpr int kSlots = kBlock / G;
     const int lane = threadIdx.x % kWave;
-    const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
     if (b < m.item_blocks) {
         const int64_t s = (int64_t)b * kSlots + threadIdx.x / G;
         Vec<VEC> pacc;
@@ -420,9 +419,11 @@ __device__ __forceinline__ void cpn_block(const CpnMode<N> &m, int b, bool first
                 pseg = cpn_walk<N, VEC, G, U, CpnSlot<N, VEC, G, U, RAG>>(m, s, lane, first_mode, lsum,
                                                                      pacc);
         }
+        const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
         store_chunk_partial<VEC, G>(pseg, pacc, m.s.part, m.s.plan.chunk_ord, s, m.s.k, col,
                                     on);
     } else {
+        const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
         zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
     }
 }
