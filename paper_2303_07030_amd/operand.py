@@ -8,6 +8,8 @@ builders; this module only allocates torch tensors and calls the binding.
 """
 from __future__ import annotations
 
+import contextlib
+
 import numpy as np
 import torch
 
@@ -18,6 +20,20 @@ def _dev(a, dtype, device):
     if isinstance(a, torch.Tensor):
         return a.to(device=device, dtype=dtype)
     return torch.from_numpy(np.ascontiguousarray(a)).to(device=device, dtype=dtype)
+
+
+def _allocate_on(stream, device):
+    """Scratch of a call that only enqueues work on `stream` (a torch stream or
+    a raw handle; None: torch's current one) is allocated in this context: the
+    allocator then reuses its memory in that stream's order.  Allocated on
+    another stream it could be handed out again, or still be in use there,
+    while the work runs."""
+    if stream is None:
+        return contextlib.nullcontext()
+    if isinstance(stream, int):
+        stream = (torch.cuda.ExternalStream(stream, device=device) if stream
+                  else torch.cuda.default_stream(device))
+    return torch.cuda.stream(stream)
 
 
 def build_plan(nseg, nnz, segptr, item_len, device, stream=None):
@@ -140,7 +156,9 @@ class DeviceCsr:
         against 0.62 for the gather of single words), else nsd_gather_f32."""
         valT = torch.empty(max(self.nnz, 1), dtype=torch.float32, device=self.val.device)
         if self.csc is not None and self.csc.to_csc.n:
-            nsd.nsd_permute_f32(self.to_csc, self.val, valT, torch.empty_like(valT), stream)
+            with _allocate_on(stream, valT.device):
+                staging = torch.empty_like(valT)
+            nsd.nsd_permute_f32(self.to_csc, self.val, valT, staging, stream)
         else:
             nsd.nsd_gather_f32(self.nnz, self.perm, self.val, valT, stream)
         return valT[: self.nnz]
