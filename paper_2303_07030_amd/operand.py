@@ -191,21 +191,26 @@ def lex_order(coords, dims, ws, stream=None):
     dev = coords[0].device
     m_ = max(n, 1)
     perm = None
-    for m in reversed(range(len(coords))):
-        key = coords[m]
-        if perm is not None:
-            key = torch.empty(m_, dtype=torch.int32, device=dev)
-            nsd.nsd_gather_i32(n, perm, coords[m], key, stream)
-        segptr = torch.empty(int(dims[m]) + 1, dtype=torch.int32, device=dev)
-        segidx = torch.empty(m_, dtype=torch.int32, device=dev)
-        p = torch.empty(m_, dtype=torch.int32, device=dev)
-        nsd.nsd_coo_mode_index(n, int(dims[m]), key, segptr, segidx, p, ws, stream)
-        if perm is None:
-            perm = p
-        else:
-            composed = torch.empty(m_, dtype=torch.int32, device=dev)
-            nsd.nsd_gather_i32(n, p, perm, composed, stream)
-            perm = composed
+    # The last gather may still run when this returns: the arrays that only
+    # this function holds, and the ones it composed, belong to its stream.
+    with _allocate_on(stream, dev):
+        for m in reversed(range(len(coords))):
+            key = coords[m]
+            if perm is not None:
+                key = torch.empty(m_, dtype=torch.int32, device=dev)
+                nsd.nsd_gather_i32(n, perm, coords[m], key, stream)
+            segptr = torch.empty(int(dims[m]) + 1, dtype=torch.int32, device=dev)
+            segidx = torch.empty(m_, dtype=torch.int32, device=dev)
+            p = torch.empty(m_, dtype=torch.int32, device=dev)
+            nsd.nsd_coo_mode_index(n, int(dims[m]), key, segptr, segidx, p, ws, stream)
+            if perm is None:
+                perm = p
+            else:
+                composed = torch.empty(m_, dtype=torch.int32, device=dev)
+                nsd.nsd_gather_i32(n, p, perm, composed, stream)
+                perm = composed
+    if stream is not None and perm.is_cuda:
+        perm.record_stream(torch.cuda.current_stream(dev))  # the caller's
     return perm[:n]
 
 

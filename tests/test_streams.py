@@ -55,6 +55,22 @@ def test_staging_of_values_in_csc_order_belongs_to_the_call(owners, monkeypatch,
     assert seen == [(owner, stream)]
 
 
+@pytest.mark.parametrize("stream, owner", [(None, None), ("side", "side")])
+def test_arrays_of_lex_order_belong_to_the_call(owners, monkeypatch, stream, owner):
+    """Every array that a gather still reads or writes when lex_order returns."""
+    coords = [torch.zeros(4, dtype=torch.int32) for _ in range(3)]
+    held = {c.data_ptr() for c in coords}
+    seen = []
+
+    def gather(n, perm, src, dst, s):
+        seen.extend(owners[t.data_ptr()] for t in (perm, src, dst) if t.data_ptr() not in held)
+
+    monkeypatch.setattr(nsd, "nsd_gather_i32", gather)
+    monkeypatch.setattr(nsd, "nsd_coo_mode_index", lambda *a: None)
+    operand.lex_order(coords, (2, 2, 2), None, stream)
+    assert len(seen) == 10 and set(seen) == {owner}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("raw", [False, True])
 def test_values_in_csc_order_on_a_side_stream(raw):
@@ -77,3 +93,21 @@ def test_values_in_csc_order_on_a_side_stream(raw):
     torch.cuda.synchronize()
     assert np.array_equal(valT.cpu().numpy(), val[A.perm.cpu().numpy()])
     assert all(torch.isnan(t).all().item() for t in taken)
+
+
+@pytest.mark.gpu
+def test_lex_order_on_a_side_stream():
+    """The current stream takes memory of the sorts' arrays' size at once."""
+    rng = np.random.default_rng(4)
+    n, dims = 300_000, (70, 40, 500)
+    key = rng.choice(int(np.prod(dims)), n, replace=False)
+    coords = [c.astype(np.int32) for c in np.unravel_index(key, dims)]
+    dev = [torch.from_numpy(c).cuda() for c in coords]
+    ws = torch.empty(nsd.nsd_build_workspace_size(n, max(dims)), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    perm = operand.lex_order(dev, dims, ws, side)
+    taken = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(6)]
+    torch.cuda.synchronize()
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(key, kind="stable"))
+    assert all((t == -1).all().item() for t in taken)
