@@ -299,6 +299,12 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads) void radix_hist_kernel(
 // by run, so consecutive lanes store consecutive addresses of a digit's output
 // range instead of scattering single words; every thread keeps the output
 // positions of the slots that it writes.
+// Bound by those writes.  The registers decide how many tiles are in flight:
+// two blocks of 512 threads to a CU take 128 a thread at most, and with three
+// payloads the compiler spilled at that (digits kept apart from the ranks that
+// hold them, 64-bit addresses of every round); made opaque and relative to the
+// wave's start the kernel takes 98.  COO -> CSR on MI355X, with the spills and
+// without: 1.02 and 0.95 ms for 9M entries (five passes), 4.58 and 4.18 for 50M.
 // Payloads carried with the keys: in[j] NULL is the element's own index.
 // Carrying what a caller would otherwise gather through the sort's
 // permutation (one random 4-byte read per element) costs 8 more bytes per
@@ -324,27 +330,36 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kern
     __shared__ int wave_tot[kWaves];
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t tile = xcd_contiguous_tile();
+    const bool mine = tid * kPer < kBins;
+    int first[kPer];  // output positions of the tile's first elements of a digit
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int d = tid * kPer + j;
+        first[j] = mine && d < 1 << bits ? offs[(int64_t)d * ntiles + tile] : 0;
+    }
     for (int i = tid; i < kWaves * kBins; i += kThreads) (&wcnt[0][0])[i] = 0;
     __syncthreads();
 
     const int64_t tile0 = tile * kTile;
     const int64_t base = tile0 + (int64_t)wave * (kSortRounds * kWave);
+    const int left = (int)min<int64_t>(kSortRounds * kWave, n - base);  // the wave's elements
     int key[kSortRounds], val[NP][kSortRounds];
     int rank[kSortRounds];  // digit << 16 | rank in the wave
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
-        const int64_t q = base + (int64_t)i * kWave + lane;
-        const bool valid = q < n;
-        key[i] = valid ? sort_load<NT>(kin + q) : 0;
+        const int o = i * kWave + lane;
+        const bool valid = o < left;
+        key[i] = valid ? sort_load<NT>(kin + base + o) : 0;
 #pragma unroll
         for (int j = 0; j < NP; ++j)
-            val[j][i] = valid ? (pl.in[j] ? sort_load<NT>(pl.in[j] + q) : (int32_t)q) : 0;
+            val[j][i] =
+                valid ? (pl.in[j] ? sort_load<NT>(pl.in[j] + base + o) : (int32_t)base + o) : 0;
     }
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
-        const bool valid = base + (int64_t)i * kWave + lane < n;
+        const bool valid = i * kWave + lane < left;
         const int d = key_digit(key[i], val[0][i], lo_bits, shift, bits);
         uint64_t same = __ballot(valid);
 #pragma unroll
@@ -356,6 +371,7 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kern
         const int below = __popcll(same & __lanemask_lt());
         const int prev = valid ? wcnt[wave][d] : 0;
         rank[i] = d << 16 | (prev + below);
+        opaque(rank[i]);  // the digit is taken from it again, not kept as well
         __builtin_amdgcn_wave_barrier();
         if (valid && below == 0) wcnt[wave][d] = (uint16_t)(prev + __popcll(same));
         __builtin_amdgcn_wave_barrier();
@@ -364,7 +380,6 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kern
     // per digit: waves' offsets inside the digit's run, then the run starts
     // (exclusive scan of the digit totals over the tile)
     int tot[kPer], sum = 0;
-    const bool mine = tid * kPer < kBins;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         tot[j] = 0;
@@ -394,7 +409,7 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kern
         const int d = tid * kPer + j;
         if (mine) {
             tile_start[d] = (uint16_t)start;
-            out_base[d] = d < 1 << bits ? offs[(int64_t)d * ntiles + tile] - start : 0;
+            out_base[d] = first[j] - start;
         }
         start += tot[j];
     }
@@ -403,10 +418,9 @@ __global__ __launch_bounds__(SortShape<NT>::kThreads, 4) void radix_scatter_kern
     int lpos[kSortRounds];  // each element's staging slot (its digit run, its rank)
 #pragma unroll
     for (int i = 0; i < kSortRounds; ++i) {
-        const int64_t q = base + (int64_t)i * kWave + lane;
         const int d = rank[i] >> 16;
         lpos[i] = -1;
-        if (q < n) {
+        if (i * kWave + lane < left) {
             lpos[i] = tile_start[d] + wcnt[wave][d] + (rank[i] & 0xffff);
             sdig[lpos[i]] = (uint16_t)d;
             sval[lpos[i]] = key[i];

@@ -95,6 +95,11 @@ __device__ __forceinline__ float lane_xor(float v) {
     }
 }
 
+// Makes x a value that the compiler may not equate with its earlier self: what
+// follows from it is computed again (an addition, a shift) where it is needed
+// instead of kept in registers of its own across the phases of a kernel.
+__device__ __forceinline__ void opaque(int &x) { asm volatile("" : "+v"(x)); }
+
 template <int VEC>
 struct Vec;
 

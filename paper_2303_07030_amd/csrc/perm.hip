@@ -192,11 +192,6 @@ __global__ __launch_bounds__(kPermThreads) void perm_hist_kernel(int64_t n, cons
         hist[(int64_t)f * ntiles + t] = (int32_t)((wcount[f >> 1] >> ((f & 1) * 16)) & 0xffffu);
 }
 
-// A value the compiler may not equate with its earlier self: the rounds'
-// indices and digits are recomputed in each phase (an addition, a shift)
-// instead of kept in 32 registers each across the phases.
-__device__ __forceinline__ void perm_opaque(int &x) { asm volatile("" : "+v"(x)); }
-
 // Keeps the compiler from moving work across every fourth unrolled round: it
 // hoists all rounds' loads otherwise and spills (128 registers a thread in a
 // block of 1024).
@@ -277,7 +272,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_sort_kernel(
         if (tid < 256) dstart[tid] -= total;
         __syncthreads();
         int shift = sh;
-        perm_opaque(shift);
+        opaque(shift);
 #pragma unroll
         for (int i = 0; i < kPermPer; ++i) {
             const uint32_t d = (v[i] >> shift) & 255u;
@@ -285,7 +280,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_sort_kernel(
             perm_keep_order(i);
         }
         __syncthreads();
-        perm_opaque(first);
+        opaque(first);
 #pragma unroll
         for (int i = 0; i < kPermPer; ++i) v[i] = tile[first + i * kWave];
     }
@@ -305,7 +300,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_sort_kernel(
         else hi = mid;
     }
     int open = lo;
-    perm_opaque(first);
+    opaque(first);
     int32_t far[kPermPer];
 #pragma unroll
     for (int i = 0; i < kPermPer; ++i) {
@@ -327,7 +322,7 @@ __global__ __launch_bounds__(kPermThreads) void perm_sort_kernel(
     }
     __syncthreads();
     // the far ends' offsets in their windows, by near offset, then by slot
-    perm_opaque(first);
+    opaque(first);
     uint16_t *low = reinterpret_cast<uint16_t *>(tile);
 #pragma unroll
     for (int i = 0; i < kPermPer; ++i) {
