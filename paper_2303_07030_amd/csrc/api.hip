@@ -222,7 +222,7 @@ static nsd_status col_dual_run(const nsd_csr *A, const DualPass &pass, double *l
         f.npass = 1;
         DualPass &p = f.pass[0];
         p.s.k = w;
-        p.s.ld = k;
+        p.ld = k;
         if (p.s.X) p.s.X += c0;
         p.own += c0;
         p.s.out += c0;
@@ -232,8 +232,8 @@ static nsd_status col_dual_run(const nsd_csr *A, const DualPass &pass, double *l
         }
         f.loss_part = last && loss ? loss_part : nullptr;
         f.loss_beta = beta;
-        NSD_TRY(dual_fused(c0 ? kDualLinAdd : kDualLin, f, NSD_KERNEL_DUAL,
-                           last ? job : LossJob{}, st));
+        const int kind = c0 ? kDualSliceAdd : last ? kDualLin : kDualSlice;
+        NSD_TRY(dual_fused(kind, f, NSD_KERNEL_DUAL, last ? job : LossJob{}, st));
     }
     return NSD_OK;
 }

@@ -13,9 +13,10 @@
 //                        dA = <C_i, B_j> of L = 1/2 ||A B||^2; with O = H,
 //                        X = G it is the whole bilinear layer
 //                        L = sum (A H) o G: dA = <G_i, H_j>, dH = A^T G.
-//                        kDualLinAdd: the same for a later slice of the
-//                        columns of rows wider than a slot, d_p including the
-//                        product over the columns before (sdd[pos_p] so far).
+//                        kDualSlice, kDualSliceAdd: the same for the first
+//                        and a later slice of the columns of rows wider than a
+//                        slot, the later one's d_p including the product over
+//                        the columns before (sdd[pos_p] so far).
 //   residual (kDualMf):  c_p = r_p = w_p - d_p, loss += r_p^2: the row and
 //                        column passes of sparse matrix factorisation.
 // These are the paper's sums over the stored keys of A with the dense rows
@@ -63,7 +64,8 @@ struct DualSlot {
 #endif
 
     __device__ __forceinline__ DualSlot(const DualPass &m_, int64_t s_, int lane_, double &ls)
-        : m(m_), s(s_), k(m_.s.stride()), lane(lane_), g(lane_ % G), lsum(ls) {
+        : m(m_), s(s_), k(dual_sliced(KIND) ? m_.ld : m_.s.k), lane(lane_), g(lane_ % G),
+          lsum(ls) {
         const SgrParams &a = m.s;
         const LaneCols lc = lane_cols<VEC, RAG>(g, 0, a.k);  // k <= G * VEC on this path
         col = lc.col;
@@ -169,7 +171,7 @@ struct DualSlot {
                 constexpr int kRep = G / U;
                 const int us = g / kRep;  // the entry whose total this lane holds
                 if (g % kRep == 0 && p + us < b0) {
-                    if constexpr (KIND == kDualLinAdd) tot += m.sdd[ps];
+                    if constexpr (KIND == kDualSliceAdd) tot += m.sdd[ps];
                     if (m.sdd) m.sdd[ps] = m.sdd_alpha * tot;
                     if (m.count_loss) lsum += (double)ws * tot;
                 }
@@ -221,7 +223,8 @@ __device__ __forceinline__ void dual_block(const DualPass &m, int b, double &lsu
                                     on);
     } else {
         const auto [col, dup, on] = lane_cols<VEC, RAG>(threadIdx.x % G, 0, m.s.k);
-        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on);
+        zero_segment<VEC>(m.s, (int64_t)(b - m.item_blocks) * kSlots + threadIdx.x / G, col, on,
+                          dual_sliced(KIND) ? m.ld : m.s.k);
     }
 }
 
@@ -299,9 +302,12 @@ static nsd_status launch_dual(DualParams f, int probe_id, LossJob job, hipStream
         NSD_TRY(check_launch("dual_kernel"));
     }
     FixJobs fx;
-    for (int i = 0; i < f.npass; ++i) add_fix(fx, f.pass[i].s);
+    for (int i = 0; i < f.npass; ++i) {
+        add_fix(fx, f.pass[i].s);
+        fx.job[i].ld = f.pass[i].ld;
+    }
     fx.loss = job;
-    return launch_fixes<VEC, G>(fx, st);
+    return launch_fixes<VEC, G, dual_sliced(KIND)>(fx, st);
 }
 
 template <int KIND>
@@ -314,6 +320,19 @@ struct DualLauncher {
     nsd_status operator()() { return launch_dual<KIND, VEC, G, RAG>(f, probe_id, job, st); }
 };
 
+// Slices of wider rows are of 32 or 64 lanes.
+template <int KIND>
+static nsd_status dual_slice(const DualLauncher<KIND> &f, const WidthPlan &wp) {
+    DualLauncher<KIND> fn = f;
+    if (wp.g == 32)
+        return wp.ragged ? fn.template operator()<4, 32, true>()
+                         : fn.template operator()<4, 32, false>();
+    if (wp.g == 64)
+        return wp.ragged ? fn.template operator()<4, 64, true>()
+                         : fn.template operator()<4, 64, false>();
+    return fail(NSD_ERR_UNSUPPORTED, "a column slice of width %d", fn.f.pass[0].s.k);
+}
+
 nsd_status dual_fused(int kind, DualParams f, int probe_id, LossJob job, hipStream_t st) {
     const WidthPlan wp = width_plan(f.pass[0].s.k);
     if (f.pass[0].s.k > kMaxFusedWidth)
@@ -322,17 +341,9 @@ nsd_status dual_fused(int kind, DualParams f, int probe_id, LossJob job, hipStre
         DualLauncher<kDualMf> fn{f, probe_id, job, st};
         return dispatch_width(wp, fn);
     }
-    if (kind == kDualLinAdd) {
-        // slices of wider rows are of 32 or 64 lanes
-        DualLauncher<kDualLinAdd> fn{f, probe_id, job, st};
-        if (wp.g == 32)
-            return wp.ragged ? fn.template operator()<4, 32, true>()
-                             : fn.template operator()<4, 32, false>();
-        if (wp.g == 64)
-            return wp.ragged ? fn.template operator()<4, 64, true>()
-                             : fn.template operator()<4, 64, false>();
-        return fail(NSD_ERR_UNSUPPORTED, "a column slice of width %d", f.pass[0].s.k);
-    }
+    if (kind == kDualSlice) return dual_slice(DualLauncher<kDualSlice>{f, probe_id, job, st}, wp);
+    if (kind == kDualSliceAdd)
+        return dual_slice(DualLauncher<kDualSliceAdd>{f, probe_id, job, st}, wp);
     DualLauncher<kDualLin> fn{f, probe_id, job, st};
     return dispatch_width(wp, fn);
 }

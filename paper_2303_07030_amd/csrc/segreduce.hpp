@@ -16,10 +16,6 @@ struct SgrParams {
     const float *X = nullptr;         // gathered dense operand (NULL: ones)
     float alpha = 1.f;
     float *out = nullptr;             // [nseg x k]
-    // Floats from one row of X, out (and a dual pass's own rows) to the next
-    // where the pass takes k columns of wider rows (dual passes; 0: k)
-    int32_t ld = 0;
-    __host__ __device__ int64_t stride() const { return ld ? ld : k; }
     float *part = nullptr;            // chunk partials (sgr_part_bytes)
     // Rows of `part` that hold a long segment's partials: its first chunk's
     // and, past it, those of the chunks at item indexes divisible by
@@ -71,14 +67,20 @@ struct LossJob {
 // dense row `own` (see dual.hip):
 //   d_p = <own[seg_p], X[idx_p]>,  out[seg] = alpha * sum_p c_p X[idx_p],
 // with c_p = w_p (kDualLin; then sdd[pos_p] = sdd_alpha * d_p when sdd is
-// set, and loss += w_p d_p when count_loss; kDualLinAdd: the same, where
-// sdd[pos_p] holds the product over the columns before this pass's and d_p
-// includes it there) or c_p = w_p - d_p (kDualMf;
+// set, and loss += w_p d_p when count_loss) or c_p = w_p - d_p (kDualMf;
 // loss += c_p^2 when count_loss).  pos_p = wperm[p] when the weights are
 // permuted, else p.
+// kDualSlice is kDualLin over k of the columns of wider rows, which lie `ld`
+// floats apart in X, out and own; kDualSliceAdd the same where sdd[pos_p] holds
+// the product over the columns before, which d_p then includes.  They are
+// kinds of their own: with the rows' distance a value of every kernel (read
+// from its arguments for the zeroed rows alone) the order-3 CP pass lost 1.4 to
+// 2.7 % (10M entries, rank 48: 917 -> 927 us) and every small call 0.2 us.
 constexpr int kDualLin = 0;
 constexpr int kDualMf = 1;
-constexpr int kDualLinAdd = 2;
+constexpr int kDualSlice = 2;
+constexpr int kDualSliceAdd = 3;
+constexpr bool dual_sliced(int kind) { return kind == kDualSlice || kind == kDualSliceAdd; }
 
 struct DualPass {
     SgrParams s;
@@ -87,6 +89,7 @@ struct DualPass {
     float sdd_alpha = 1.f;
     int32_t count_loss = 0;
     int32_t item_blocks = 0, empty_blocks = 0;  // set by the launcher
+    int32_t ld = 0;                             // kDualSlice, kDualSliceAdd
 };
 
 struct DualParams {

@@ -328,12 +328,18 @@ __device__ __forceinline__ int sgr_walk(const SgrParams &a, int64_t s, int col, 
 }
 
 template <int VEC>
-__device__ __forceinline__ void zero_segment(const SgrParams &a, int64_t e, int col, bool on) {
+__device__ __forceinline__ void zero_segment(const SgrParams &a, int64_t e, int col, bool on,
+                                             int64_t ld) {
     if (e < a.plan.nempty && on) {
         Vec<VEC> z;
         z.zero();
-        z.store(a.out + a.plan.empty_seg[e] * a.stride() + col);
+        z.store(a.out + a.plan.empty_seg[e] * ld + col);
     }
+}
+
+template <int VEC>
+__device__ __forceinline__ void zero_segment(const SgrParams &a, int64_t e, int col, bool on) {
+    zero_segment<VEC>(a, e, col, on, a.k);
 }
 
 struct NoSegDone {
@@ -393,7 +399,8 @@ __device__ __forceinline__ void loss_total_block(const LossJob &job) {
 // segment of at most kHugeChunks partial rows; the blocks after them (when
 // launched) give a whole block to each huge segment with more.  When
 // seg_loss is given, beta * ||out[seg]||^2 is stored for every long segment.
-// b is the block's index within the pass.
+// ld: floats from one row of out to the next; b: the block's index within the
+// pass.
 #ifdef NSD_FIX_DEPTH
 constexpr int kFixDepth = NSD_FIX_DEPTH;
 #else
@@ -401,7 +408,7 @@ constexpr int kFixDepth = 4;  // chunk partials in flight per lane (a power of t
 #endif
 
 template <int VEC, int G>
-__device__ __forceinline__ void fix_block(const SgrParams &a, int b, int wave_blocks,
+__device__ __forceinline__ void fix_block(const SgrParams &a, int64_t ld, int b, int wave_blocks,
                                           double *seg_loss, double beta) {
     constexpr int RG = kWave / G;  // row groups per wave
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -484,7 +491,7 @@ __device__ __forceinline__ void fix_block(const SgrParams &a, int b, int wave_bl
         }
         if ((!huge || wave == 0) && q == 0 && on) {
             acc[0].scale(a.alpha);
-            acc[0].store(a.out + seg * a.stride() + col);
+            acc[0].store(a.out + seg * ld + col);
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 if (e >= dup) lsq += (double)acc[0].v[e] * acc[0].v[e];
@@ -504,6 +511,7 @@ constexpr int kMaxFixJobs = NSD_MAX_ORDER;
 
 struct FixJob {
     SgrParams a;
+    int32_t ld = 0;  // combines of column slices
     double *seg_loss = nullptr;
     double beta = 0.0;
     int wave_blocks = 0, blocks = 0;
@@ -527,7 +535,8 @@ constexpr int kFixSumChains = NSD_FIX_SUM_CHAINS;
 constexpr int kFixSumChains = 16;
 #endif
 
-template <int VEC, int G>
+// SLICE: the rows of out are wider than the jobs' columns (FixJob::ld).
+template <int VEC, int G, bool SLICE = false>
 __global__ __launch_bounds__(kBlock) void sgr_fix_kernel(FixJobs f) {
     if (f.loss.loss && blockIdx.x == gridDim.x - 1) {
         loss_total_block<kFixSumChains>(f.loss);
@@ -537,7 +546,7 @@ __global__ __launch_bounds__(kBlock) void sgr_fix_kernel(FixJobs f) {
     for (int t = 0; t < f.n; ++t) {
         const FixJob &j = f.job[t];
         if (b < j.blocks) {
-            fix_block<VEC, G>(j.a, b, j.wave_blocks, j.seg_loss, j.beta);
+            fix_block<VEC, G>(j.a, SLICE ? j.ld : j.a.k, b, j.wave_blocks, j.seg_loss, j.beta);
             return;
         }
         b -= j.blocks;
@@ -595,13 +604,13 @@ inline void add_fix(FixJobs &f, const SgrParams &a, double *seg_loss = nullptr,
 
 // Combines the long segments of every pass in f (those that have any) and
 // runs the loss job (when given), all in one launch.
-template <int VEC, int G>
+template <int VEC, int G, bool SLICE = false>
 inline nsd_status launch_fixes(const FixJobs &f, hipStream_t st) {
     int grid = 0;
     for (int t = 0; t < f.n; ++t) grid += f.job[t].blocks;
     if (grid == 0 && !f.loss.loss) return NSD_OK;
     probe_begin(NSD_KERNEL_SGR_FIX, st);
-    sgr_fix_kernel<VEC, G><<<grid + (f.loss.loss ? 1 : 0), kBlock, 0, st>>>(f);
+    sgr_fix_kernel<VEC, G, SLICE><<<grid + (f.loss.loss ? 1 : 0), kBlock, 0, st>>>(f);
     probe_end(NSD_KERNEL_SGR_FIX, st);
     return check_launch("sgr_fix_kernel");
 }
