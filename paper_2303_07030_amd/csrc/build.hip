@@ -470,7 +470,10 @@ static int digit_bits(int bits) {
 
 size_t sort_ws_bytes(int64_t n, int32_t max_key, int np) {
     Carver c(nullptr);
-    const int64_t bins = sort_tiles(n) << kWideDigitBits;
+    // the tiles of n or of the largest sort below it in smaller tiles, so that a
+    // workspace sized for n entries holds any sort of fewer
+    const int64_t bins = std::max(sort_tiles(n), sort_tiles(std::min(n, kSortStreamMin - 1)))
+                         << kWideDigitBits;
     c.take<int32_t>(n);  // ping keys
     c.take<int32_t>(n);  // pong keys
     for (int j = 0; j < np; ++j) {

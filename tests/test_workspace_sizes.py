@@ -1,0 +1,21 @@
+"""Size queries (host only): a workspace sized for one input serves every
+smaller one of its kind."""
+import pytest
+
+from paper_2303_07030_amd import nsd
+
+# around the sizes at which the sort, its scans and its tiles change
+SIZES = sorted({max(n + d, 0) for n in (0, 4096, 2048 * 2048, 1 << 22, 1 << 23, 1 << 24, 50_000_000)
+                for d in (-8193, -1, 0, 1, 4097)})
+
+
+@pytest.mark.parametrize("query", [
+    lambda n: nsd.nsd_build_workspace_size(n, 1000),
+    lambda n: nsd.nsd_build_workspace_size(n, 2**30),
+    lambda n: nsd.nsd_ttv_build_workspace_size(3, (1000, 1000, 1000), n),
+    lambda n: nsd.nsd_validate_coo_workspace_size((1000, 1000, 1000), n),
+    nsd.nsd_perm_plan_workspace_size,
+], ids=["build", "build_wide_keys", "ttv_build", "validate_coo", "perm_plan"])
+def test_builders_workspace_grows_with_the_entries(query):
+    sizes = [query(n) for n in SIZES]
+    assert sizes == sorted(sizes)
