@@ -49,12 +49,12 @@ static size_t round256(size_t b) { return (b + 255) & ~size_t(255); }
 // (passes that run in one launch need both), then the loss partials and the
 // long-row loss partials.
 static size_t row_part_bytes(const nsd_csr *A, int k) {
-    return round256(sgr_part_bytes(A->plan, std::max(k, 1)));
+    return round256(sgr_part_bytes(A->plan, A->nnz, std::max(k, 1)));
 }
 
 static size_t part_region_bytes(const nsd_csr *A, const nsd_csc *At, int k) {
     size_t b = row_part_bytes(A, k);
-    if (At) b += round256(sgr_part_bytes(At->plan, std::max(k, 1)));
+    if (At) b += round256(sgr_part_bytes(At->plan, At->nnz, std::max(k, 1)));
     return b;
 }
 
@@ -63,7 +63,7 @@ static size_t loss_part_count(const nsd_csr *A, const nsd_csc *At, int k) {
     for (int kk : {k, 1}) m = std::max(m, sddmm_shape(A->nnz, kk).nblocks);
     if (At) {
         const nsd_plan *both[2] = {&A->plan, &At->plan};
-        m = std::max(m, dual_blocks(both, 2, k));
+        m = std::max(m, dual_blocks(both, 2, A->nnz, k));
     }
     return (size_t)m;
 }
@@ -262,7 +262,7 @@ static nsd_status check_bilinear(const nsd_csr *A, const nsd_csc *At, const floa
 // whole-wave slots at most, as the width's).
 static int64_t bilinear_loss_parts(const nsd_csc *At, int k) {
     const nsd_plan *cols[1] = {&At->plan};
-    return std::max<int64_t>(1, dual_blocks(cols, 1, k));
+    return std::max<int64_t>(1, dual_blocks(cols, 1, At->nnz, k));
 }
 
 // The loss total of an unfused SDDMM's block partials; with nnz == 0 the
@@ -507,7 +507,7 @@ nsd_status nsd_loss_bilinear_noalloc(const nsd_csr *A, const nsd_csc *At, const 
     NSD_TRY(check_bilinear(A, At, H, G, k, loss, dA, dH));
     // the layout in the static scratch: the column plan's chunk partials,
     // then the loss partials of the fused pass (or of the unfused SDDMM)
-    const size_t part = round256(sgr_part_bytes(At->plan, k));
+    const size_t part = round256(sgr_part_bytes(At->plan, At->nnz, k));
     const size_t need = part + round256(bilinear_loss_parts(At, k) * sizeof(double));
     if (need > kScratchBytes)
         return fail(NSD_ERR_WORKSPACE,
@@ -650,7 +650,7 @@ static size_t cp_ws_bytes(const nsd_coo3 *X, int rank) {
     size_t b = 0;
     nsd_plan plans[3];
     for (int n = 0; n < 3; ++n) {
-        b += round256(sgr_part_bytes(X->mode[n].plan, std::max(rank, 1)));
+        b += round256(sgr_part_bytes(X->mode[n].plan, X->nnz, std::max(rank, 1)));
         plans[n] = X->mode[n].plan;
     }
     int64_t blocks = cp_blocks(plans, rank);
@@ -669,7 +669,7 @@ static nsd_status cp_wide(const nsd_coo3 *X, const float *const *F, int rank, fl
     float *part[3];
     for (int n = 0; n < 3; ++n) {
         part[n] = reinterpret_cast<float *>(b);
-        b += round256(sgr_part_bytes(X->mode[n].plan, rank));
+        b += round256(sgr_part_bytes(X->mode[n].plan, X->nnz, rank));
     }
     double *loss_part = reinterpret_cast<double *>(b);
     nsd_plan plans[3] = {X->mode[0].plan, X->mode[1].plan, X->mode[2].plan};
@@ -759,7 +759,7 @@ nsd_status nsd_loss_cp(const nsd_coo3 *X, const float *F1, const float *F2, cons
         m.s.alpha = -seed;
         m.s.out = dF[n];
         m.s.part = reinterpret_cast<float *>(b);
-        b += round256(sgr_part_bytes(md.plan, rank));
+        b += round256(sgr_part_bytes(md.plan, X->nnz, rank));
         m.idx_b = md.idx_b;
         m.own = F[n];
         m.fa = F[(n + 1) % 3];

@@ -515,7 +515,7 @@ static int64_t cpn_loss_parts(const nsd_coon *X, int rank) {
 // fused slot, the residual of every stored entry.
 static size_t cpn_ws_bytes(const nsd_coon *X, int rank) {
     size_t b = 0;
-    for (int n = 0; n < X->order; ++n) b += rnd256(sgr_part_bytes(X->mode[n].plan, rank));
+    for (int n = 0; n < X->order; ++n) b += rnd256(sgr_part_bytes(X->mode[n].plan, X->nnz, rank));
     b += rnd256(cpn_loss_parts(X, rank) * sizeof(double));
     if (rank > kMaxFusedWidth) b += rnd256((size_t)std::max(X->nnz, 1) * sizeof(float));
     return b;
@@ -531,7 +531,7 @@ static nsd_status cpn_wide(const nsd_coon *X, const float *const *F, int32_t ran
     float *part[NSD_MAX_ORDER];
     for (int n = 0; n < N; ++n) {
         part[n] = reinterpret_cast<float *>(b);
-        b += rnd256(sgr_part_bytes(X->mode[n].plan, rank));
+        b += rnd256(sgr_part_bytes(X->mode[n].plan, X->nnz, rank));
     }
     double *loss_part = reinterpret_cast<double *>(b);
     b += rnd256(cpn_loss_parts(X, rank) * sizeof(double));
@@ -617,7 +617,7 @@ static nsd_status cpn_run(const nsd_coon *X, const float *const *F, int32_t rank
         m.s.alpha = -seed;
         m.s.out = dF[n];
         m.s.part = reinterpret_cast<float *>(b);
-        b += rnd256(sgr_part_bytes(md.plan, rank));
+        b += rnd256(sgr_part_bytes(md.plan, X->nnz, rank));
         for (int o = 0; o < N - 1; ++o) {
             m.other[o] = md.idx[o];
             m.fac[o] = F[(n + 1 + o) % N];

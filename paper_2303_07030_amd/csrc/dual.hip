@@ -264,15 +264,13 @@ constexpr int dual_unroll() {
 #endif
 }
 
-int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k) {
+int64_t dual_blocks(const nsd_plan *const *plans, int npass, int64_t nnz, int k) {
     const WidthPlan wp = width_plan(k);
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < npass; ++i)
         n += ceil_div(plans[i]->nitems, slots) + ceil_div(plans[i]->nempty, slots);
-    if (k == 1)  // a linear pass runs by tiles (vec1.hip)
-        for (int i = 0; i < npass; ++i) n = std::max(n, vec1_max_tiles(*plans[i]));
-    return n;
+    return k == 1 ? std::max(n, vec1_max_tiles(nnz)) : n;  // a linear pass's tiles (vec1.hip)
 }
 
 template <int KIND, int VEC, int G, bool RAG>

@@ -194,8 +194,8 @@ struct JvpLauncher {
 static_assert(kJvpGroup + 1 <= kMaxFixJobs, "a group's combine jobs fit one launch");
 
 // Bytes of one output's chunk partials, rounded to 256.
-static size_t jvp_part_bytes(const nsd_plan &plan, int32_t k) {
-    return (sgr_part_bytes(plan, k) + 255) & ~size_t(255);
+static size_t jvp_part_bytes(const nsd_csr *A, int32_t k) {
+    return (sgr_part_bytes(A->plan, A->nnz, k) + 255) & ~size_t(255);
 }
 
 static nsd_status check_jvp_csr(const nsd_csr *A, int32_t k) {
@@ -241,7 +241,7 @@ nsd_status nsd_spmm_jvp(const nsd_csr *A, const float *dAval, const float *B, co
     NSD_REQUIRE(A->nrows == 0 || (C && dC), "C/dC is NULL");
     if (A->nnz > 0) NSD_REQUIRE(dAval && B && dB, "dA/B/dB is NULL");
     hipStream_t st = as_stream(stream);
-    const size_t half = jvp_part_bytes(A->plan, k);
+    const size_t half = jvp_part_bytes(A, k);
     if (ws == nullptr || ws_bytes < 2 * half)
         return fail(NSD_ERR_WORKSPACE, "workspace %zu bytes at %p, need %zu", ws_bytes, ws,
                     2 * half);
@@ -266,7 +266,7 @@ nsd_status nsd_spmm_jvp(const nsd_csr *A, const float *dAval, const float *B, co
 nsd_status nsd_spmm_jvp_batch_workspace_size(const nsd_csr *A, int32_t k, size_t *bytes) {
     NSD_REQUIRE(bytes != nullptr, "bytes is NULL");
     NSD_TRY(check_jvp_csr(A, k));
-    *bytes = (size_t)(kJvpGroup + 1) * jvp_part_bytes(A->plan, k);
+    *bytes = (size_t)(kJvpGroup + 1) * jvp_part_bytes(A, k);
     return NSD_OK;
 }
 
@@ -278,7 +278,7 @@ nsd_status nsd_spmm_jvp_batch(const nsd_csr *A, int32_t m, const float *dAval, c
     NSD_REQUIRE(A->nrows == 0 || m == 0 || dC != nullptr, "dC is NULL");
     if (A->nnz > 0) NSD_REQUIRE(B != nullptr, "B is NULL");
     hipStream_t st = as_stream(stream);
-    const size_t one = jvp_part_bytes(A->plan, k);
+    const size_t one = jvp_part_bytes(A, k);
     const size_t need = (size_t)(kJvpGroup + 1) * one;
     if (ws == nullptr || ws_bytes < need)
         return fail(NSD_ERR_WORKSPACE, "workspace %zu bytes at %p, need %zu", ws_bytes, ws,

@@ -57,9 +57,9 @@ __global__ void fill_zero_kernel(float *out, int64_t n) {
 
 // One partial row per chunk item (compact, see store_chunk_partial); at width
 // 1 the two words per tile of vec1.hip's passes, where those are more.
-size_t sgr_part_bytes(const nsd_plan &plan, int k) {
+size_t sgr_part_bytes(const nsd_plan &plan, int64_t nnz, int k) {
     const size_t chunks = (size_t)std::max<int64_t>(plan.nchunks, 1) * (size_t)k * sizeof(float);
-    return k > 1 ? chunks : std::max(chunks, 2 * sizeof(float) * (size_t)vec1_max_tiles(plan));
+    return k > 1 ? chunks : std::max(chunks, 2 * sizeof(float) * (size_t)vec1_max_tiles(nnz));
 }
 
 template <int VEC, int G>

@@ -50,7 +50,7 @@ int choose_slot_len(int64_t nnz, int slots_per_wave);
 
 // Entries per thread of the width-1 sampled product.
 constexpr int kVec1SddmmEntries = 8;
-size_t sgr_part_bytes(const nsd_plan &plan, int k);
+size_t sgr_part_bytes(const nsd_plan &plan, int64_t nnz, int k);
 nsd_status segreduce(SgrParams a, hipStream_t st);
 
 // The loss total, run by one extra block of the last kernel of a call:
@@ -101,7 +101,7 @@ struct DualParams {
                                   // run by one extra block (when early.loss is set)
 };
 
-int64_t dual_blocks(const nsd_plan *const *plans, int npass, int k);
+int64_t dual_blocks(const nsd_plan *const *plans, int npass, int64_t nnz, int k);
 // The widths that a slot of one wave holds.
 constexpr int kMaxFusedWidth = 256;
 // Launches the passes and their long-segment combines, the last of which
@@ -153,12 +153,13 @@ nsd_status sddmm(SddmmParams a, hipStream_t st);
 // sums the pass's own loss; `entries`: the operand's rows, columns and values
 // in its own order with the dense operands, from which a small pass forms it)
 // and the sampled product in `nblocks` blocks.
-// vec1_max_tiles bounds the tiles, one loss partial and two floats each.
+// vec1_max_tiles bounds the tiles of passes over up to nnz entries, one loss
+// partial and two floats each.
 nsd_status vec1_reduce(const SgrParams &a, LossJob job, hipStream_t st);
 nsd_status vec1_dual(const DualPass &m, const SddmmParams &entries, double *loss_part,
                      int probe_id, LossJob job, hipStream_t st);
 nsd_status vec1_sddmm(const SddmmParams &a, int64_t nblocks, hipStream_t st);
-int64_t vec1_max_tiles(const nsd_plan &plan);
+int64_t vec1_max_tiles(int64_t nnz);
 
 nsd_status loss_finalize(const double *part, int64_t n, double *loss, hipStream_t st);
 

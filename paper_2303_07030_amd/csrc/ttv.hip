@@ -100,7 +100,7 @@ static nsd_status check_ttv(const nsd_ttv_plan *T) {
 }
 
 static size_t ttv_ws(const nsd_ttv_plan *T) {
-    const size_t a = sgr_part_bytes(T->yplan, 1), b = sgr_part_bytes(T->lplan, 1);
+    const size_t a = sgr_part_bytes(T->yplan, T->nnz, 1), b = sgr_part_bytes(T->lplan, T->nnz, 1);
     return ((std::max(a, b) + 255) & ~size_t(255));
 }
 
@@ -125,7 +125,7 @@ static SgrParams ttv_sgr(int32_t nseg, int32_t nnz, const nsd_plan &plan, const 
 }
 
 static size_t ttm_ws(const nsd_ttv_plan *T, int32_t R) {
-    const size_t a = sgr_part_bytes(T->yplan, R), b = sgr_part_bytes(T->lplan, R);
+    const size_t a = sgr_part_bytes(T->yplan, T->nnz, R), b = sgr_part_bytes(T->lplan, T->nnz, R);
     return ((std::max(a, b) + 255) & ~size_t(255));
 }
 

@@ -328,11 +328,10 @@ static int64_t vec1_tile(int64_t nnz) {
     return kBlock * (nnz < kVec1Short ? 2 : 8);
 }
 
-// An item holds at most 2 L + min(L, 32) entries (see the plan builder), so
-// this many entries at most are in a plan, in tiles of the shortest length.
-int64_t vec1_max_tiles(const nsd_plan &plan) {
-    const int64_t L = plan.item_len, per = 2 * L + (L < 32 ? L : 32);
-    return ceil_div(std::max<int64_t>(plan.nitems, 1) * per, 2 * kBlock) + 1;
+// The most tiles of a pass over up to nnz entries.
+int64_t vec1_max_tiles(int64_t nnz) {
+    const int64_t n = std::max<int64_t>(nnz, 1), few = std::min(n, kVec1Short - 1);
+    return std::max(ceil_div(n, vec1_tile(n)), ceil_div(few, vec1_tile(few)));
 }
 
 template <int T, int E, bool DUAL, bool SMALL>

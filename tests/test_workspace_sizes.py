@@ -19,3 +19,18 @@ SIZES = sorted({max(n + d, 0) for n in (0, 4096, 2048 * 2048, 1 << 22, 1 << 23, 
 def test_builders_workspace_grows_with_the_entries(query):
     sizes = [query(n) for n in SIZES]
     assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("csc", [False, True])
+@pytest.mark.parametrize("item_len, nitems", [(2, 2**29), (16, 2**26), (256, 2**22)])
+def test_width_one_partials_follow_the_entries(item_len, nitems, csc):
+    """The tiles of a width-1 pass are of entries (2,048 each of this many):
+    two floats and a loss partial a tile whatever the plan's items, beside
+    what the other passes of the width need."""
+    nnz, ptr = 2**29, 0x1000  # no pointer is read
+    plan = nsd.nsd_plan(item_len, nitems, 0, 0, 0, 0, ptr, 0, 0, 0, 0, 0)
+    A = nsd.nsd_csr(nitems, nitems, nnz, ptr, ptr, ptr, ptr)
+    At = nsd.nsd_csc(nitems, nitems, nnz, ptr, ptr, ptr, ptr)
+    A.plan = At.plan = plan
+    one, two = (nsd.nsd_workspace_size(A, At if csc else None, k) for k in (1, 2))
+    assert one <= two + 2 * 16 * (nnz // 2048) + 1024
