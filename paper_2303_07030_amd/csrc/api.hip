@@ -259,20 +259,20 @@ static nsd_status check_bilinear(const nsd_csr *A, const nsd_csc *At, const floa
 }
 
 // Loss partials of the bilinear layer: one per block of its column pass (of
-// whole-wave slots at most, as the width's).
+// whole-wave slots at most, as the width's), or of its sampled product.
 static int64_t bilinear_loss_parts(const nsd_csc *At, int k) {
     const nsd_plan *cols[1] = {&At->plan};
-    return std::max<int64_t>(1, dual_blocks(cols, 1, At->nnz, k));
+    int64_t m = std::max<int64_t>(1, dual_blocks(cols, 1, At->nnz, k));
+    if (k > kMaxFusedWidth) m = std::max(m, sddmm_shape(At->nnz, k).nblocks);
+    return m;
 }
 
-// The loss total of an unfused SDDMM's block partials; with nnz == 0 the
-// loss is 0.
-static nsd_status finish_loss(const SddmmParams &p, double *loss, hipStream_t st);
+// The loss total of a sampled product's block partials; with nnz == 0 there
+// are none and the loss is 0.
+static nsd_status finish_loss(const SddmmParams &p, double *loss, hipStream_t st) {
+    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k).nblocks, loss, st);
+}
 
-// The bilinear layer L = sum (A H) o G with its gradients, given the chunk
-// partials of the column plan and the loss partials; with valT, gradT and
-// staging (nnz floats each) A's values are moved to CSC order and the sparse
-// gradient back by the CSC's two-pass permutations.
 // With the CSC's two-pass permutations (large patterns), a column pass reads
 // A's values moved to CSC order and writes its sampled products there, so
 // its entry positions are its own slots; csc_order_after moves the products
@@ -293,6 +293,41 @@ static nsd_status csc_order_after(const nsd_csc *At, float *valT, const float *g
     return nsd_permute_f32(&At->to_csr, gradT, dA, staging, st);
 }
 
+// Rows wider than a slot are taken in column slices where a slice gathers at
+// least this many floats.  Below, the time is the latency of the launches, two
+// a slice, and the sampled product and the gather-reduce of their own win; the
+// line goes with the slice's width because narrow slices leave lanes idle.
+// A VJP on MI355X, slices against the two, us: k = 512 (slices of 256) 27 / 21
+// at 10K entries, 54 / 50 at 65K, 67 / 73 at 100K, 141 / 202 at 300K; k = 300
+// (of 150) 27 / 20, 50 / 40, 62 / 56, 127 / 141; k = 2048 at 10K 116 / 61.
+constexpr int64_t kSliceMin = int64_t(20) << 20;
+
+// The gradients of a linear column pass and its loss (NULL: none), the
+// sampled products into dA in A's order; with valT, gradT and staging (nnz
+// floats each) through the CSC's two-pass permutations.
+static nsd_status col_gradients(const nsd_csr *A, const nsd_csc *At, DualPass pass, float *dA,
+                                double *loss_part, double *loss, double beta, float *valT,
+                                float *gradT, float *staging, hipStream_t st) {
+    const int64_t slices = ceil_div(pass.s.k, kMaxFusedWidth);
+    if (slices > 1 && A->nnz * (pass.s.k / slices) < kSliceMin) {
+        SddmmParams sp = sddmm_params(A, pass.s.X, pass.own, pass.s.k, pass.sdd_alpha, dA);
+        if (loss) {
+            sp.w = A->val;
+            sp.beta = beta;
+            sp.part = loss_part;
+        }
+        NSD_TRY(sddmm(sp, st));
+        if (loss) NSD_TRY(finish_loss(sp, loss, st));
+        return segreduce(pass.s, st);
+    }
+    NSD_TRY(csc_order_before(A, At, valT, gradT, staging, pass, st));
+    NSD_TRY(col_dual_run(A, pass, loss_part, loss, st, beta));
+    return csc_order_after(At, valT, gradT, staging, dA, st);
+}
+
+// The bilinear layer L = sum (A H) o G with its gradients, given the chunk
+// partials of the column plan, the loss partials and (or NULL) the arrays of
+// the two-pass permutations.
 static nsd_status bilinear_run(const nsd_csr *A, const nsd_csc *At, const float *H,
                                const float *G, int k, float seed, double *loss, float *dA,
                                float *dH, float *part_col, double *loss_part, hipStream_t st,
@@ -301,10 +336,9 @@ static nsd_status bilinear_run(const nsd_csr *A, const nsd_csc *At, const float 
     if (A->nnz > 0) {
         // one pass over the columns: own row H_j, gathered row G_i:
         // dA[p] = seed <G_i, H_j>, loss = sum_p A_p <G_i, H_j>, dH = seed A^T G
-        DualPass pass = col_dual(A, At, G, H, k, seed, dH, part_col, dA, seed, true);
-        NSD_TRY(csc_order_before(A, At, valT, gradT, staging, pass, st));
-        NSD_TRY(col_dual_run(A, pass, loss_part, loss, st));
-        return csc_order_after(At, valT, gradT, staging, dA, st);
+        return col_gradients(A, At,
+                             col_dual(A, At, G, H, k, seed, dH, part_col, dA, seed, true), dA,
+                             loss_part, loss, 1.0, valT, gradT, staging, st);
     }
     // no entries: a loss of 0, dH = 0
     NSD_TRY(loss_finalize(loss_part, 0, loss, st));
@@ -338,12 +372,6 @@ static nsd_status scratch_base(char **out) {
     }
     *out = static_cast<char *>(g_scratch[dev]);
     return NSD_OK;
-}
-
-// The loss partial count of a fused SDDMM; with nnz == 0 the loss is 0.
-static nsd_status finish_loss(const SddmmParams &p, double *loss, hipStream_t st) {
-    // with nnz == 0 there are no partials and the finaliser writes 0
-    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k).nblocks, loss, st);
 }
 
 }  // namespace nsd
@@ -474,11 +502,9 @@ nsd_status nsd_loss_frob_spmm(const nsd_csr *A, const nsd_csc *At, const float *
     // forward: C = A B
     NSD_TRY(segreduce(rows_params(A, B, k, 1.f, C, w.part), st));
     if (A->nnz > 0 && k > 1) {
-        // dB and dA in column slices, the loss as 1/2 sum_p A_p <C_i, B_j>
-        DualPass cols = col_dual(A, At, C, B, k, seed, dB, w.part_col, dA, seed, true);
-        NSD_TRY(csc_order_before(A, At, w.valT, w.gradT, w.staging, cols, st));
-        NSD_TRY(col_dual_run(A, cols, w.loss_part, loss, st, 0.5));
-        return csc_order_after(At, w.valT, w.gradT, w.staging, dA, st);
+        // dB and dA, the loss as 1/2 sum_p A_p <C_i, B_j>
+        return col_gradients(A, At, col_dual(A, At, C, B, k, seed, dB, w.part_col, dA, seed, true),
+                             dA, w.loss_part, loss, 0.5, w.valT, w.gradT, w.staging, st);
     }
     // dA = seed * <C_i, B_j> on the pattern; loss = 1/2 sum_p A_p <C_i, B_j> = 1/2 ||C||^2
     SddmmParams sp = sddmm_params(A, C, B, k, seed, dA);
@@ -506,7 +532,7 @@ nsd_status nsd_loss_bilinear_noalloc(const nsd_csr *A, const nsd_csc *At, const 
                                      float *dA, float *dH, void *stream) {
     NSD_TRY(check_bilinear(A, At, H, G, k, loss, dA, dH));
     // the layout in the static scratch: the column plan's chunk partials,
-    // then the loss partials of the fused pass (or of the unfused SDDMM)
+    // then the loss partials
     const size_t part = round256(sgr_part_bytes(At->plan, At->nnz, k));
     const size_t need = part + round256(bilinear_loss_parts(At, k) * sizeof(double));
     if (need > kScratchBytes)
@@ -532,10 +558,8 @@ nsd_status nsd_spmm_vjp(const nsd_csr *A, const nsd_csc *At, const float *X, con
     if (A->nnz > 0) {
         // one pass over the columns: own row X_j, gathered row G_i (NULL:
         // ones): dA[p] = <G_i, X_j>, dX = A^T G; no loss
-        DualPass pass = col_dual(A, At, G, X, k, 1.f, dX, w.part_col, dA, 1.f, false);
-        NSD_TRY(csc_order_before(A, At, w.valT, w.gradT, w.staging, pass, st));
-        NSD_TRY(col_dual_run(A, pass, w.loss_part, nullptr, st));
-        return csc_order_after(At, w.valT, w.gradT, w.staging, dA, st);
+        return col_gradients(A, At, col_dual(A, At, G, X, k, 1.f, dX, w.part_col, dA, 1.f, false),
+                             dA, w.loss_part, nullptr, 1.0, w.valT, w.gradT, w.staging, st);
     }
     return segreduce(cols_params(A, At, G, k, 1.f, dX, w.part_col), st);
 }

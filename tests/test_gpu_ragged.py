@@ -151,3 +151,42 @@ def test_column_slices(nsd, orc, k, perm_plans):
     assert_mag_close(dHg, -0.5 * dX, 0.5 * dXm, what="dH")
     check_frob(orc, nrows, ncols, rowptr, colind, val, X, k, run_frob(nsd, A, X, k, seed=3.0),
                seed=3.0)
+
+
+@pytest.mark.parametrize("perm_plans", [False, True])
+@pytest.mark.parametrize("k", [257, 260, 512, 1027])
+def test_column_slices_of_larger_patterns(nsd, k, perm_plans):
+    """Patterns of which a slice gathers at least 20 * 2**20 floats are taken
+    in column slices (above: a sampled product and a gather-reduce of their
+    own); against dense products in 64 bits."""
+    from paper_2303_07030_amd.operand import DeviceCsr
+    rng = np.random.default_rng(k)
+    nrows, ncols = 420, 500
+    dense = rng.standard_normal((nrows, ncols)) * (rng.random((nrows, ncols)) < 0.8)
+    dense[:, [0, 77]], dense[5] = 0.0, 0.0  # empty columns and an empty row
+    rows, cols = np.nonzero(dense)
+    rowptr = np.concatenate([[0], np.cumsum((dense != 0).sum(1))]).astype(np.int32)
+    val = dense[rows, cols].astype(np.float32)
+    assert len(val) * (k // -(-k // 256)) >= 20 << 20
+    dense[rows, cols] = val
+    A = DeviceCsr(nrows, ncols, rowptr, cols.astype(np.int32), val, k_hint=k,
+                  perm_plans=perm_plans)
+    X = rng.standard_normal((ncols, k)).astype(np.float32)
+    G = rng.standard_normal((nrows, k)).astype(np.float32)
+    x, g = X.astype(np.float64), G.astype(np.float64)
+    dA, dAm = (g @ x.T)[rows, cols], (abs(g) @ abs(x).T)[rows, cols]
+    dX, dXm = dense.T @ g, abs(dense).T @ abs(g)
+    got, gotX = torch.full((A.nnz,), np.nan, device="cuda"), empty_offset((ncols, k))
+    nsd.nsd_spmm_vjp(A.desc, A.csc, dev_offset(X), dev(G), k, got, gotX, A.workspace(k))
+    assert_mag_close(host(got), dA, dAm, what="vjp dA")
+    assert_mag_close(host(gotX), dX, dXm, what="vjp dX")
+    Lg, dAg, dHg = run_bilinear(nsd, A, X, G, k, seed=-0.5)
+    assert_mag_close(Lg, (val * dA).sum(), (abs(val) * dAm).sum(), what="loss")
+    assert_mag_close(dAg, -0.5 * dA, 0.5 * dAm, what="dA")
+    assert_mag_close(dHg, -0.5 * dX, 0.5 * dXm, what="dH")
+    C, Cm = dense @ x, abs(dense) @ abs(x)
+    Cf, Lf, dAf, dBf = run_frob(nsd, A, X, k)
+    assert_mag_close(Cf, C, Cm, what="C")
+    assert_mag_close(Lf, 0.5 * (C * C).sum(), 0.5 * (Cm * Cm).sum(), what="frob loss")
+    assert_mag_close(dAf, (C @ x.T)[rows, cols], (Cm @ abs(x).T)[rows, cols], what="frob dA")
+    assert_mag_close(dBf, dense.T @ C, abs(dense).T @ Cm, what="frob dB")
