@@ -29,7 +29,9 @@ namespace nsd {
 
 // ------------------------------------------------------------ residual
 
-template <int N, int VEC, int G, int U>
+// RAG: the rank is no multiple of four.  As a run-time value its selects cost
+// whole quads 5 to 20 % (10K entries, k = 2048: 114 -> 130 us a call).
+template <int N, int VEC, int G, int U, bool RAG>
 __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
     static_assert(G == kWave, "one slot per wave");
     constexpr int kSlots = kBlock / G;
@@ -53,7 +55,7 @@ __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
 #pragma unroll
             for (int u = 0; u < U; ++u) part[u] = 0.f;
             for (int c0 = 0; c0 < a.k; c0 += G * VEC) {
-                const auto [col, dup, on] = lane_cols<VEC>(g, c0, a.k);
+                const auto [col, dup, on] = lane_cols<VEC, RAG>(g, c0, a.k);
                 if (on) {
                     Vec<VEC> t[U];
 #pragma unroll
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
 #pragma unroll
                     for (int u = 0; u < U; ++u)
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) part[u] += e >= dup ? t[u].v[e] : 0.f;
+                        for (int e = 0; e < VEC; ++e) part[u] += !RAG || e >= dup ? t[u].v[e] : 0.f;
                 }
             }
             // lane g ends with the model value of entry g / (G / U)
@@ -91,20 +93,20 @@ __global__ __launch_bounds__(kBlock) void resid_kernel(ResidParams a) {
     if (threadIdx.x == 0) a.part[blockIdx.x] = t;
 }
 
-template <int N, int VEC>
+template <int N, bool RAG>
 static nsd_status launch_resid(ResidParams a, int64_t nblocks, hipStream_t st) {
-    resid_kernel<N, VEC, kWave, 4><<<(unsigned)nblocks, kBlock, 0, st>>>(a);
+    resid_kernel<N, 4, kWave, 4, RAG><<<(unsigned)nblocks, kBlock, 0, st>>>(a);
     return check_launch("resid_kernel");
 }
 
-template <int VEC>
+template <bool RAG>
 static nsd_status resid_order(ResidParams a, int64_t nblocks, hipStream_t st) {
     switch (a.order) {
-        case 2: return launch_resid<2, VEC>(a, nblocks, st);
-        case 3: return launch_resid<3, VEC>(a, nblocks, st);
-        case 4: return launch_resid<4, VEC>(a, nblocks, st);
-        case 5: return launch_resid<5, VEC>(a, nblocks, st);
-        default: return launch_resid<6, VEC>(a, nblocks, st);
+        case 2: return launch_resid<2, RAG>(a, nblocks, st);
+        case 3: return launch_resid<3, RAG>(a, nblocks, st);
+        case 4: return launch_resid<4, RAG>(a, nblocks, st);
+        case 5: return launch_resid<5, RAG>(a, nblocks, st);
+        default: return launch_resid<6, RAG>(a, nblocks, st);
     }
 }
 
@@ -117,7 +119,8 @@ nsd_status resid_pass(ResidParams a, hipStream_t st) {
         return fail(NSD_ERR_UNSUPPORTED, "residual pass of width %d below one wave", a.k);
     a.L = sh.L;
     a.nslots = (int32_t)sh.nslots;
-    return resid_order<4>(a, sh.nblocks, st);
+    return sh.wp.ragged ? resid_order<true>(a, sh.nblocks, st)
+                        : resid_order<false>(a, sh.nblocks, st);
 }
 
 // ------------------------------------------------------ mode gather-reduce
