@@ -60,7 +60,8 @@ static size_t part_region_bytes(const nsd_csr *A, const nsd_csc *At, int k) {
 
 static size_t loss_part_count(const nsd_csr *A, const nsd_csc *At, int k) {
     int64_t m = std::max<int64_t>(1, frob_row_blocks(A->plan, k));
-    for (int kk : {k, 1}) m = std::max(m, sddmm_shape(A->nnz, kk).nblocks);
+    for (int kk : {k, 1})
+        for (bool whole : {true, false}) m = std::max(m, sddmm_shape(A->nnz, kk, whole).nblocks);
     if (At) {
         const nsd_plan *both[2] = {&A->plan, &At->plan};
         m = std::max(m, dual_blocks(both, 2, A->nnz, k));
@@ -263,14 +264,14 @@ static nsd_status check_bilinear(const nsd_csr *A, const nsd_csc *At, const floa
 static int64_t bilinear_loss_parts(const nsd_csc *At, int k) {
     const nsd_plan *cols[1] = {&At->plan};
     int64_t m = std::max<int64_t>(1, dual_blocks(cols, 1, At->nnz, k));
-    if (k > kMaxFusedWidth) m = std::max(m, sddmm_shape(At->nnz, k).nblocks);
+    if (k > kMaxFusedWidth) m = std::max(m, sddmm_shape(At->nnz, k, false).nblocks);
     return m;
 }
 
 // The loss total of a sampled product's block partials; with nnz == 0 there
 // are none and the loss is 0.
 static nsd_status finish_loss(const SddmmParams &p, double *loss, hipStream_t st) {
-    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k).nblocks, loss, st);
+    return loss_finalize(p.part, sddmm_shape(p.nnz, p.k, sddmm_whole(p)).nblocks, loss, st);
 }
 
 // With the CSC's two-pass permutations (large patterns), a column pass reads
@@ -468,7 +469,7 @@ nsd_status nsd_loss_sum_spmv(const nsd_csr *A, const nsd_csc *At, const float *x
     }
     LossJob job;
     job.p1 = w.loss_part;
-    job.n1 = sddmm_shape(A->nnz, 1).nblocks;
+    job.n1 = sddmm_shape(A->nnz, 1, false).nblocks;
     job.loss = loss;
     return vec1_reduce(cols, job, st);
 }

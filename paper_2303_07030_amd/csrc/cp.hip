@@ -258,7 +258,7 @@ constexpr int cp_unroll() {
 }
 
 int64_t cp_blocks(const nsd_plan *plans, int rank) {
-    const WidthPlan wp = width_plan(rank);
+    const WidthPlan wp = narrow_plan(rank, false, kCpScalarWidth);  // the layout of more blocks
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < 3; ++i) n += ceil_div(plans[i].nitems, slots) + ceil_div(plans[i].nempty, slots);
@@ -292,6 +292,7 @@ static nsd_status launch_cp(CpParams f, double *loss, hipStream_t st) {
 }
 
 struct CpLauncher {
+    static constexpr int kMin = 1, kScalar = kCpScalarWidth, kRagged = 5;
     CpParams f;
     double *loss;
     hipStream_t st;
@@ -301,7 +302,10 @@ struct CpLauncher {
 
 nsd_status cp_fused(CpParams f, double *loss, hipStream_t st) {
     CpLauncher fn{f, loss, st};
-    return dispatch_width(width_plan(f.m[0].s.k), fn);
+    const SgrParams &s = f.m[0].s;
+    bool whole = true;
+    for (const CpMode &m : f.m) whole = whole && whole_quads(s.k, {m.own, m.s.out});
+    return dispatch_width(cp_plan(s.k, whole, s.nnz, s.plan.item_len), fn);
 }
 
 }  // namespace nsd

@@ -485,6 +485,7 @@ static nsd_status launch_cpn(CpnParams<N> f, double *loss, hipStream_t st) {
 
 template <int N>
 struct CpnLauncher {
+    static constexpr int kMin = 1, kScalar = kCpScalarWidth, kRagged = 5;
     CpnParams<N> f;
     double *loss;
     hipStream_t st;
@@ -493,7 +494,7 @@ struct CpnLauncher {
 };
 
 static int64_t cpn_blocks(const nsd_coon *X, int rank) {
-    const WidthPlan wp = width_plan(rank);
+    const WidthPlan wp = narrow_plan(rank, false, kCpScalarWidth);  // the layout of more blocks
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < X->order; ++i)
@@ -638,7 +639,9 @@ static nsd_status cpn_run(const nsd_coon *X, const float *const *F, int32_t rank
     }
     f.loss_part = reinterpret_cast<double *>(b);
     CpnLauncher<N> fn{f, loss, st};
-    return dispatch_width(width_plan(rank), fn);
+    bool whole = true;
+    for (int n = 0; n < N; ++n) whole = whole && whole_quads(rank, {F[n], dF[n]});
+    return dispatch_width(cp_plan(rank, whole, X->nnz, X->mode[0].plan.item_len), fn);
 }
 
 }  // namespace nsd

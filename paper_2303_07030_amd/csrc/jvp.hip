@@ -183,8 +183,20 @@ static nsd_status launch_jvp(JvpParams<MB> f, hipStream_t st) {
     return launch_fixes<VEC, G>(fx, st);
 }
 
+// One column per lane up to 32 columns of the smallest patterns and of those
+// between 2^17 and 2^20 entries (two tangents, k = 17 to 31, one column against
+// four a lane, us: 3K entries 8.8 / 10.6, 30K 16 / 15, 200K 28 / 31, 1M 93 to 110
+// / 87 to 114, 6M 557 to 651 / 524 to 667).
+constexpr int kJvpScalarWidth = 32;
+
+static WidthPlan jvp_plan(int k, int64_t nnz, std::initializer_list<const void *> rows) {
+    const bool scalar = nnz < (1 << 14) || (nnz >= (1 << 17) && nnz < (1 << 20));
+    return narrow_plan(k, whole_quads(k, rows), scalar ? kJvpScalarWidth : kScalarWidth);
+}
+
 template <int MB>
 struct JvpLauncher {
+    static constexpr int kMin = 1, kScalar = kJvpScalarWidth, kRagged = kScalarWidth + 1;
     JvpParams<MB> f;
     hipStream_t st;
     template <int VEC, int G, bool RAG>
@@ -260,7 +272,7 @@ nsd_status nsd_spmm_jvp(const nsd_csr *A, const float *dAval, const float *B, co
         return segreduce(f.d[0], st);
     }
     JvpLauncher<1> fn{f, st};
-    return dispatch_width(width_plan(k), fn);
+    return dispatch_width(jvp_plan(k, A->nnz, {B, dB, C, dC}), fn);
 }
 
 nsd_status nsd_spmm_jvp_batch_workspace_size(const nsd_csr *A, int32_t k, size_t *bytes) {
@@ -284,6 +296,7 @@ nsd_status nsd_spmm_jvp_batch(const nsd_csr *A, int32_t m, const float *dAval, c
         return fail(NSD_ERR_WORKSPACE, "workspace %zu bytes at %p, need %zu", ws_bytes, ws,
                     need);
     char *w = static_cast<char *>(ws);
+    const WidthPlan wp = jvp_plan(k, A->nnz, {B, dB, C, dC});
     const int64_t nnz = A->nnz, xstride = (int64_t)A->ncols * k, ostride = (int64_t)A->nrows * k;
     // groups of tangents, C with the first (or alone when m == 0)
     for (int32_t t0 = 0; t0 < m || (t0 == 0 && C != nullptr); t0 += kJvpGroup) {
@@ -306,7 +319,7 @@ nsd_status nsd_spmm_jvp_batch(const nsd_csr *A, int32_t m, const float *dAval, c
             continue;
         }
         JvpLauncher<kJvpGroup> fn{f, st};
-        NSD_TRY(dispatch_width(width_plan(k), fn));
+        NSD_TRY(dispatch_width(wp, fn));
     }
     return NSD_OK;
 }

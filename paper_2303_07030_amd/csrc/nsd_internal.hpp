@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstddef>
 #include <cstdint>
+#include <initializer_list>
 
 #include "nsd.h"
 
@@ -176,23 +177,47 @@ struct Vec<1> {
 // Dense width k -> (VEC, G): VEC fp32 per lane, G lanes per dense row chunk.
 // Rows of four columns and more take four per lane, whatever the width and
 // the alignment: in a width that is no multiple of four the last lane steps
-// back to the row's last four columns (lane_cols).
+// back to the row's last four columns (lane_cols).  Narrow rows may take one
+// column per lane instead (narrow_plan).
 struct WidthPlan {
-    int vec;   // 4, or 1 below four columns
+    int vec;   // 4, or 1
     int g;     // lanes per row chunk, power of two, <= 64
     int chunk; // columns covered by one chunk = vec * g
     bool ragged;  // the last lane steps back (k no multiple of vec)
 };
 
-inline WidthPlan width_plan(int k) {
+inline WidthPlan lane_plan(int k, int vec) {
     WidthPlan p;
-    p.vec = k >= 4 ? 4 : 1;
+    p.vec = vec;
     const int64_t lanes = ceil_div(k, p.vec);
     p.g = 1;
     while (p.g < lanes && p.g < 64) p.g <<= 1;
     p.chunk = p.vec * p.g;
     p.ragged = k % p.vec != 0;
     return p;
+}
+
+inline WidthPlan width_plan(int k) { return lane_plan(k, k >= 4 ? 4 : 1); }
+
+// Rows of whole quads of columns at 16-byte addresses (a NULL: no rows).
+inline bool whole_quads(int k, std::initializer_list<const void *> rows) {
+    if (k % 4 != 0) return false;
+    for (const void *p : rows)
+        if (reinterpret_cast<uintptr_t>(p) & 15) return false;
+    return true;
+}
+
+// Rows up to kScalarWidth columns that are not of whole quads take one column
+// per lane.  Measured on MI355X, one column against four a lane, us: at k = 7
+// the SpMM of 1M entries 21 / 29, a bilinear step 48 / 70, the factorisation
+// 43 / 75, a sampled product of 10K entries 4.4 / 9.5; at 13 29 / 31, 51 / 81,
+// 69 / 86 and 4.5 / 5.0; from 17 on the quads win (41 / 28, 76 / 59, 108 / 62
+// at 17 to 18).  A slot of four or eight lanes walks four times as many
+// items per wave as one of sixteen, each waiting for the others' segment ends.
+constexpr int kScalarWidth = 16;
+
+inline WidthPlan narrow_plan(int k, bool whole, int scalar = kScalarWidth) {
+    return k <= scalar && !whole ? lane_plan(k, 1) : width_plan(k);
 }
 
 // ------------------------------------------- shared internal operations

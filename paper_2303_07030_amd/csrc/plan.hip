@@ -354,7 +354,7 @@ nsd_status nsd_plan_item_len(int32_t nnz, int32_t k, int32_t *item_len) {
     // one slot of a wave (a slot covers min(k, 256) columns); measured on
     // MI355X this is within 2% of the best length for every workload shape
     // tried (1M to 60M entries, k = 32 to 256)
-    const WidthPlan wp = width_plan(k);
+    const WidthPlan wp = narrow_plan(k, k % 4 == 0);
     const int64_t slots = 32768LL * (kWave / wp.g);
     int32_t L = 16;
     while (L < 256 && (int64_t)L * 2 * slots <= nnz) L <<= 1;

@@ -77,6 +77,7 @@ static nsd_status launch_sgr_vg(SgrParams a, hipStream_t st) {
 }
 
 struct SgrLauncher {
+    static constexpr int kMin = 2, kScalar = kScalarWidth, kRagged = kScalarWidth + 1;
     SgrParams a;
     hipStream_t st;
     template <int VEC, int G, bool RAG>
@@ -91,7 +92,7 @@ nsd_status segreduce(SgrParams a, hipStream_t st) {
     }
     if (a.k == 1) return vec1_reduce(a, LossJob{}, st);
     SgrLauncher f{a, st};
-    return dispatch_width(width_plan(a.k), f);
+    return dispatch_width(narrow_plan(a.k, whole_quads(a.k, {a.X, a.out})), f);
 }
 
 // ------------------------------------------------------------------ SDDMM
@@ -183,9 +184,15 @@ int choose_slot_len(int64_t nnz, int slots_per_wave) {
     return L;
 }
 
-SddmmShape sddmm_shape(int64_t nnz, int k) {
+// One column per lane also up to 32 columns of large patterns: the rows are
+// cold there, and the sampled product of 6M entries at k = 18 to 31 takes 187 to
+// 232 us so, 205 to 277 with quads (1M entries: 32 to 35 against 23 to 33).
+constexpr int kSddmmScalarWidth = 32;
+constexpr int64_t kSddmmLarge = int64_t(1) << 22;
+
+SddmmShape sddmm_shape(int64_t nnz, int k, bool whole) {
     SddmmShape sh;
-    sh.wp = width_plan(k);
+    sh.wp = narrow_plan(k, whole, nnz >= kSddmmLarge ? kSddmmScalarWidth : kScalarWidth);
     if (k == 1) {  // entry by entry (vec1.hip): a slot is a thread's entries
         sh.L = kVec1SddmmEntries;
         sh.nslots = ceil_div(nnz, sh.L);
@@ -199,7 +206,10 @@ SddmmShape sddmm_shape(int64_t nnz, int k) {
     return sh;
 }
 
+bool sddmm_whole(const SddmmParams &a) { return whole_quads(a.k, {a.X, a.Y}); }
+
 struct SddmmLauncher {
+    static constexpr int kMin = 2, kScalar = kSddmmScalarWidth, kRagged = kScalarWidth + 1;
     SddmmParams a;
     int64_t nb;
     hipStream_t st;
@@ -213,7 +223,7 @@ struct SddmmLauncher {
 };
 
 nsd_status sddmm(SddmmParams a, hipStream_t st) {
-    const SddmmShape sh = sddmm_shape(a.nnz, a.k);
+    const SddmmShape sh = sddmm_shape(a.nnz, a.k, sddmm_whole(a));
     a.L = sh.L;
     a.nslots = (int32_t)sh.nslots;
     if (sh.nblocks == 0) return NSD_OK;
@@ -385,12 +395,13 @@ static nsd_status launch_frob(FrobParams f, hipStream_t st) {
 }
 
 int64_t frob_row_blocks(const nsd_plan &rows, int k) {
-    const WidthPlan wp = width_plan(k);
+    const WidthPlan wp = narrow_plan(k, false);  // the layout of more blocks
     const int slots = kBlock / wp.g;
     return ceil_div(rows.nitems, slots) + ceil_div(rows.nempty, slots);
 }
 
 struct FrobLauncher {
+    static constexpr int kMin = 2, kScalar = kScalarWidth, kRagged = kScalarWidth + 1;
     FrobParams f;
     hipStream_t st;
     template <int VEC, int G, bool RAG>
@@ -399,7 +410,8 @@ struct FrobLauncher {
 
 nsd_status frob_fused(FrobParams f, hipStream_t st) {
     FrobLauncher fn{f, st};
-    return dispatch_width(width_plan(f.rows.k), fn);
+    const bool whole = whole_quads(f.rows.k, {f.rows.X, f.rows.out, f.cols.s.out});
+    return dispatch_width(narrow_plan(f.rows.k, whole), fn);
 }
 
 }  // namespace nsd

@@ -139,13 +139,28 @@ struct CpParams {
     double *loss_part = nullptr;
 };
 
+constexpr int kCpScalarWidth = 32;
+
+// The lane layout of a fused CP pass over rows of `whole` quads or not, with
+// plans of items of L entries.  Its items are short and its arithmetic long, so
+// the quads win down to the narrowest ranks where there is work for them; one
+// column per lane wins where a wave's items are few (cp3 of 20K entries, rank 7,
+// us: 8.4 against 10.9; rank 13 9.2 / 9.7; rank 25 of 3K 8.6 / 9.0) or long (10M
+// entries, rank 5, items of 12: 534 / 601; rank 10 of 24: 688 / 897).
+inline WidthPlan cp_plan(int rank, bool whole, int64_t nnz, int L) {
+    const bool scalar = rank <= 8    ? L > 8 || nnz < (1 << 18)
+                        : rank <= 16 ? L > 16 || nnz < (1 << 15)
+                                     : nnz < (1 << 13);
+    return narrow_plan(rank, whole || !scalar, kCpScalarWidth);
+}
 int64_t cp_blocks(const nsd_plan *plans, int rank);
 nsd_status cp_fused(CpParams f, double *loss, hipStream_t st);
 
 int64_t frob_row_blocks(const nsd_plan &rows, int k);
 nsd_status frob_fused(FrobParams f, hipStream_t st);
 
-SddmmShape sddmm_shape(int64_t nnz, int k);
+SddmmShape sddmm_shape(int64_t nnz, int k, bool whole);
+bool sddmm_whole(const SddmmParams &a);
 nsd_status sddmm(SddmmParams a, hipStream_t st);
 
 // Width-1 passes (vec1.hip): the gather-reduce (with a loss total of earlier

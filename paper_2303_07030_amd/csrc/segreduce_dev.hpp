@@ -625,17 +625,24 @@ inline nsd_status launch_fix(const SgrParams &a, double *seg_loss, double beta, 
     return launch_fixes<VEC, G>(f, st);
 }
 
-// Calls f.template operator()<VEC, G, RAG>() for the lane layout wp.
+// Calls f.template operator()<VEC, G, RAG>() for the lane layout wp.  F names
+// what it is called with: kMin, its narrowest width; kScalar, the widest with
+// one column per lane; kRagged, the narrowest that is no multiple of four with
+// four.
 template <bool RAG, class F>
 inline nsd_status dispatch_quads(const WidthPlan &wp, F &f) {
+    constexpr int first = RAG ? F::kRagged : 5;
+    if constexpr (first <= 8)
+        if (wp.g == 2) return f.template operator()<4, 2, RAG>();
+    if constexpr (first <= 16)
+        if (wp.g == 4) return f.template operator()<4, 4, RAG>();
     switch (wp.g) {
-        case 2: return f.template operator()<4, 2, RAG>();
-        case 4: return f.template operator()<4, 4, RAG>();
         case 8: return f.template operator()<4, 8, RAG>();
         case 16: return f.template operator()<4, 16, RAG>();
         case 32: return f.template operator()<4, 32, RAG>();
-        default: return f.template operator()<4, 64, RAG>();
+        case 64: return f.template operator()<4, 64, RAG>();
     }
+    return fail(NSD_ERR_UNSUPPORTED, "no kernel of %d lanes", wp.g);
 }
 
 template <class F>
@@ -644,11 +651,17 @@ inline nsd_status dispatch_width(const WidthPlan &wp, F &f) {
         if (wp.g == 1) return f.template operator()<4, 1, false>();  // k = 4
         return wp.ragged ? dispatch_quads<true>(wp, f) : dispatch_quads<false>(wp, f);
     }
-    switch (wp.g) {  // fewer than four columns
-        case 1: return f.template operator()<1, 1, false>();
+    if constexpr (F::kMin <= 1)
+        if (wp.g == 1) return f.template operator()<1, 1, false>();
+    if constexpr (F::kScalar > 16)
+        if (wp.g == 32) return f.template operator()<1, 32, false>();
+    switch (wp.g) {
         case 2: return f.template operator()<1, 2, false>();
-        default: return f.template operator()<1, 4, false>();
+        case 4: return f.template operator()<1, 4, false>();
+        case 8: return f.template operator()<1, 8, false>();
+        case 16: return f.template operator()<1, 16, false>();
     }
+    return fail(NSD_ERR_UNSUPPORTED, "no kernel of %d lanes of a column", wp.g);
 }
 
 // Reduces U partial dot products across the G lanes of a slot with a

@@ -110,10 +110,10 @@ static nsd_status resid_order(ResidParams a, int64_t nblocks, hipStream_t st) {
     }
 }
 
-int64_t resid_blocks(int64_t nnz, int k) { return sddmm_shape(nnz, k).nblocks; }
+int64_t resid_blocks(int64_t nnz, int k) { return sddmm_shape(nnz, k, false).nblocks; }
 
 nsd_status resid_pass(ResidParams a, hipStream_t st) {
-    const SddmmShape sh = sddmm_shape(a.nnz, a.k);
+    const SddmmShape sh = sddmm_shape(a.nnz, a.k, false);
     if (sh.nblocks == 0) return NSD_OK;
     if (sh.wp.g != kWave)
         return fail(NSD_ERR_UNSUPPORTED, "residual pass of width %d below one wave", a.k);

@@ -229,6 +229,14 @@ def _stored_in_lex_order(coords, val, dims, ws, stream):
     return out, v[:n], perm
 
 
+def _cp_item_len(nnz, rank):
+    """Item length of the CP passes: 3/8 of the library's general choice (see
+    the classes below), at ranks above eight that of whole quads of columns,
+    which these passes take four per lane where the matrix passes take one."""
+    width = rank if rank <= 8 else -(-rank // 4) * 4
+    return max(8, nsd.nsd_plan_item_len(nnz, width) * 3 // 8)
+
+
 class DeviceCoo3:
     """A COO 3-tensor in HBM, stored in lexicographic (i, j, l) order (the
     order its first mode pass walks, so the residual on X's keys is written
@@ -249,7 +257,7 @@ class DeviceCoo3:
         # MI355X, 3/8 of it is best for the fused order-3 CP pass (24 entries
         # at 20M entries, rank 32: 1.05 ms per step against 1.08 at 16 and
         # 1.10 at 32)
-        self.item_len = item_len or max(8, nsd.nsd_plan_item_len(self.nnz, rank_hint) * 3 // 8)
+        self.item_len = item_len or _cp_item_len(self.nnz, rank_hint)
         self.desc = nsd.nsd_coo3()
         self.desc.dims[:] = self.dims
         self.desc.nnz = self.nnz
@@ -314,7 +322,7 @@ class DeviceCooN:
         # 3/8 of the library's general item length, as for order 3: measured
         # best on MI355X for the order-4 CP pass (24 entries at 20M entries,
         # rank 32: 1.46 ms per step against 1.51 at 16 and 1.48 at 32)
-        self.item_len = item_len or max(8, nsd.nsd_plan_item_len(self.nnz, rank_hint) * 3 // 8)
+        self.item_len = item_len or _cp_item_len(self.nnz, rank_hint)
         self.desc = nsd.nsd_coon()
         self.desc.order = N
         for m in range(N):

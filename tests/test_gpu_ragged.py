@@ -2,6 +2,9 @@
 the row's last four columns and shares some with the lane before.  Every
 remainder at the narrowest widths, at the edges of each slot size and past a
 wave's chunk, against the fp64 oracle; and a shared column that is infinite.
+The matrix passes take widths up to 16 that are not of whole quads one column
+per lane, and so do others by the number of entries: the last tests are on the
+sizes past those lines.
 """
 import numpy as np
 import pytest
@@ -190,3 +193,76 @@ def test_column_slices_of_larger_patterns(nsd, k, perm_plans):
     assert_mag_close(Lf, 0.5 * (C * C).sum(), 0.5 * (Cm * Cm).sum(), what="frob loss")
     assert_mag_close(dAf, (C @ x.T)[rows, cols], (Cm @ abs(x).T)[rows, cols], what="frob dA")
     assert_mag_close(dBf, dense.T @ C, abs(dense).T @ Cm, what="frob dB")
+
+
+def large_pattern(rng, nrows, ncols, nnz):
+    key = np.unique(rng.integers(0, nrows * ncols, nnz + nnz // 8))
+    key = np.sort(rng.permutation(key)[:nnz])
+    rows, cols = (key // ncols).astype(np.int32), (key % ncols).astype(np.int32)
+    rowptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=nrows))]).astype(np.int32)
+    return rows, rowptr, cols, rng.standard_normal(nnz).astype(np.float32)
+
+
+@pytest.mark.parametrize("nnz", [(1 << 15) + 5, (1 << 18) + 5])
+@pytest.mark.parametrize("rank", [5, 7, 9, 15, 21])
+def test_cp_of_more_entries(nsd, orc, rank, nnz):
+    """Ragged ranks in quads: from 2^15 entries on above eight, from 2^18 on
+    below (items of eight entries)."""
+    from paper_2303_07030_amd.operand import DeviceCoo3, DeviceCooN
+    dims, i, j, l, val, F = cp_case(rank, dims=(90, 70, 120), nnz=nnz)
+    X = DeviceCoo3(dims, i, j, l, val, item_len=8)
+    check_cp(orc, dims, i, j, l, val, F, rank, run_cp(nsd, X, F, rank, seed=0.75), seed=0.75)
+    if nnz < 1 << 18:
+        return
+    dims = (60, 50, 40, 9)
+    key = np.random.default_rng(rank).choice(int(np.prod(dims)), nnz, replace=False)
+    coords = [c.astype(np.int32) for c in np.unravel_index(key, dims)]
+    F = [(0.3 * np.random.default_rng(n).standard_normal((d, rank))).astype(np.float32)
+         for n, d in enumerate(dims)]
+    X = DeviceCooN(dims, coords, val, item_len=8, fibers=True)
+    check_cpn(orc, dims, coords, val, F, rank, run_cpn(nsd, X, F, rank, seed=0.5), seed=0.5)
+
+
+@pytest.mark.parametrize("k", [17, 31, 32])
+def test_sampled_product_of_more_entries(nsd, k):
+    """From 2^22 entries on up to 32 columns take one lane each (32: of rows
+    off their 16-byte lines)."""
+    from paper_2303_07030_amd.operand import DeviceCsr
+    rng = np.random.default_rng(k)
+    rows, rowptr, cols, val = large_pattern(rng, 3000, 2500, (1 << 22) + 3)
+    A = DeviceCsr(3000, 2500, rowptr, cols, val, k_hint=k, build_csc=False)
+    X = rng.standard_normal((3000, k)).astype(np.float32)
+    Y = rng.standard_normal((2500, k)).astype(np.float32)
+    out = torch.full((A.nnz,), np.nan, device="cuda")
+    nsd.nsd_sddmm(A.desc, dev_offset(X), dev_offset(Y), k, -2.0, out)
+    x, y = X.astype(np.float64), Y.astype(np.float64)
+    assert_mag_close(host(out), -2.0 * (x @ y.T)[rows, cols], 2.0 * (abs(x) @ abs(y).T)[rows, cols])
+
+
+@pytest.mark.parametrize("nnz", [(1 << 14) - 1, (1 << 14) + 1, (1 << 17) + 1])
+@pytest.mark.parametrize("k", [17, 31])
+def test_tangents_of_more_entries(nsd, k, nnz):
+    """One column a lane up to 32 columns below 2^14 entries and from 2^17 on."""
+    import scipy.sparse as sp
+    from paper_2303_07030_amd.operand import DeviceCsr
+    rng = np.random.default_rng(k)
+    nrows, ncols, m = 1500, 1300, 3
+    rows, rowptr, cols, val = large_pattern(rng, nrows, ncols, nnz)
+    A = DeviceCsr(nrows, ncols, rowptr, cols, val, k_hint=k, build_csc=False)
+    B, dB = (rng.standard_normal(s).astype(np.float32) for s in ((ncols, k), (m, ncols, k)))
+    dval = rng.standard_normal((m, nnz)).astype(np.float32)
+    C = torch.full((nrows, k), np.nan, device="cuda")
+    dC = torch.full((m, nrows, k), np.nan, device="cuda")
+    ws = torch.empty(nsd.nsd_spmm_jvp_batch_workspace_size(A.desc, k), dtype=torch.uint8,
+                     device="cuda")
+    nsd.nsd_spmm_jvp_batch(A.desc, m, dev(dval), dev(B), dev(dB), k, C, dC, ws)
+
+    def mat(v):
+        return sp.csr_matrix((v.astype(np.float64), cols, rowptr), (nrows, ncols))
+
+    S, b = mat(val), B.astype(np.float64)
+    assert_mag_close(host(C), S @ b, abs(S) @ abs(b), what="C")
+    for t in range(m):
+        D, d = mat(dval[t]), dB[t].astype(np.float64)
+        assert_mag_close(host(dC[t]), D @ b + S @ d, abs(D) @ abs(b) + abs(S) @ abs(d),
+                         what=f"dC[{t}]")
