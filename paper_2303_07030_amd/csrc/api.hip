@@ -247,6 +247,9 @@ static nsd_status col_dual_run(const nsd_csr *A, const DualPass &pass, double *l
 // 238 against 106 at 8M.
 constexpr int32_t kSmvmSplit = 1 << 18;
 
+// See nsd_loss_frob_spmm.
+constexpr int32_t kFrobSplit = 3 << 17;
+
 static nsd_status check_bilinear(const nsd_csr *A, const nsd_csc *At, const float *H,
                                  const float *G, int k, const double *loss, const float *dA,
                                  const float *dH) {
@@ -487,7 +490,14 @@ nsd_status nsd_loss_frob_spmm(const nsd_csr *A, const nsd_csc *At, const float *
     ComputeWs w;
     NSD_TRY(carve_compute(ws, ws_bytes, A, At, k, &w));
     hipStream_t st = as_stream(stream);
-    if (A->nnz > 0 && k > 1 && k <= kMaxFusedWidth) {
+    // Up to four columns, one a lane: the sampled product and the gather-reduce
+    // of their own beat the column pass of both once they are more than
+    // launches, unless that one reads and writes in CSC order (k = 3, us: 200K
+    // entries 31 against 28, 1M 67 / 85, 3M 197 / 243; with the moves 4.5M 352 /
+    // 289).
+    const bool split = k < 4 || (k == 4 && !whole_quads(k, {B, C, dB}));
+    const bool fused = k > 1 && !(split && A->nnz >= kFrobSplit && !w.valT);
+    if (A->nnz > 0 && fused && k <= kMaxFusedWidth) {
         // row pass (C and the loss), long-row combine, one column pass (dB
         // and dA, with B_j the column's own row), long-column combine, total
         FrobParams f;
@@ -502,7 +512,7 @@ nsd_status nsd_loss_frob_spmm(const nsd_csr *A, const nsd_csc *At, const float *
     }
     // forward: C = A B
     NSD_TRY(segreduce(rows_params(A, B, k, 1.f, C, w.part), st));
-    if (A->nnz > 0 && k > 1) {
+    if (A->nnz > 0 && fused) {
         // dB and dA, the loss as 1/2 sum_p A_p <C_i, B_j>
         return col_gradients(A, At, col_dual(A, At, C, B, k, seed, dB, w.part_col, dA, seed, true),
                              dA, w.loss_part, loss, 0.5, w.valT, w.gradT, w.staging, st);

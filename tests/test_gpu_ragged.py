@@ -239,6 +239,31 @@ def test_sampled_product_of_more_entries(nsd, k):
     assert_mag_close(host(out), -2.0 * (x @ y.T)[rows, cols], 2.0 * (abs(x) @ abs(y).T)[rows, cols])
 
 
+@pytest.mark.parametrize("perm_plans", [False, True])
+@pytest.mark.parametrize("k", [2, 3, 4])
+def test_frob_of_more_entries(nsd, k, perm_plans):
+    """Up to four columns (4: of rows off their 16-byte lines) go in separate
+    passes from 3 * 2^17 entries on, unless the values move to CSC order."""
+    import scipy.sparse as sp
+    from paper_2303_07030_amd.operand import DeviceCsr
+    rng = np.random.default_rng(k)
+    nrows, ncols = 9000, 7000
+    rows, rowptr, cols, val = large_pattern(rng, nrows, ncols, (3 << 17) + 7)
+    A = DeviceCsr(nrows, ncols, rowptr, cols, val, k_hint=k, perm_plans=perm_plans)
+    B = rng.standard_normal((ncols, k)).astype(np.float32)
+    C, dB = empty_offset((nrows, k)), empty_offset((ncols, k))
+    dA, loss = torch.full((A.nnz,), np.nan, device="cuda"), \
+        torch.empty(1, dtype=torch.float64, device="cuda")
+    nsd.nsd_loss_frob_spmm(A.desc, A.csc, dev_offset(B), k, 0.5, C, loss, dA, dB, A.workspace(k))
+    S, b = sp.csr_matrix((val.astype(np.float64), cols, rowptr), (nrows, ncols)), B.astype(float)
+    c, cm = S @ b, abs(S) @ abs(b)
+    assert_mag_close(host(C), c, cm, what="C")
+    assert_mag_close(host(loss)[0], 0.5 * (c * c).sum(), 0.5 * (cm * cm).sum(), what="loss")
+    assert_mag_close(host(dA), 0.5 * (c[rows] * b[cols]).sum(1),
+                     0.5 * (cm[rows] * abs(b[cols])).sum(1), what="dA")
+    assert_mag_close(host(dB), 0.5 * (S.T @ c), 0.5 * (abs(S).T @ cm), what="dB")
+
+
 @pytest.mark.parametrize("nnz", [(1 << 14) - 1, (1 << 14) + 1, (1 << 17) + 1])
 @pytest.mark.parametrize("k", [17, 31])
 def test_tangents_of_more_entries(nsd, k, nnz):
