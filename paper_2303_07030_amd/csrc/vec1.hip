@@ -307,8 +307,18 @@ __global__ __launch_bounds__(kBlock) void vec1_fix_kernel(Vec1Params f, int64_t 
     const int seg = a.segidx[e - 1];
     if (a.segidx[e] != seg || a.segptr[seg] < b * tile) return;
     const int64_t last = ((int64_t)a.segptr[seg + 1] - 1) / tile;
-    float s = 0.f;
-    for (int64_t j = b + 1 + lane; j <= last; j += kWave) s += f.head[j];
+    float s = b + 1 + lane <= last ? f.head[b + 1 + lane] : 0.f;
+    // a segment of many tiles: independent loads (a column of 50M entries has
+    // 24K heads, 121 us with one load in flight at a time, 23 so)
+    constexpr int kDeep = 16;
+    for (int64_t j0 = b + 1 + kWave + lane; j0 <= last; j0 += kDeep * kWave) {
+        float x[kDeep];
+#pragma unroll
+        for (int u = 0; u < kDeep; ++u) x[u] = f.head[min(j0 + u * kWave, last)];
+#pragma unroll
+        for (int u = 0; u < kDeep; ++u)
+            if (j0 + u * kWave <= last) s += x[u];
+    }
 #pragma unroll
     for (int m = kWave / 2; m >= 1; m >>= 1) s += __shfl_xor(s, m, kWave);
     if (lane == 0) a.out[seg] = a.alpha * (f.tail[b] + s);
