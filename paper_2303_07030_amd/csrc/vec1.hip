@@ -28,8 +28,8 @@ struct Vec1Params {
     float *sdd = nullptr;        // sampled products at the weights' positions
     float sdd_alpha = 1.f;
     double *loss_part = nullptr; // one per tile (NULL: no loss)
-    double *loss = nullptr;      // SMALL: the loss, by the first block over `entries`
-    SddmmParams entries;         // the operand's entries in their own order (SMALL)
+    double *loss = nullptr;      // WHOLE: the loss, by the first block over `entries`
+    SddmmParams entries;         // the operand's entries in their own order (WHOLE)
     float *head = nullptr, *tail = nullptr;  // [tiles]
 };
 
@@ -109,17 +109,17 @@ __device__ __forceinline__ void vec1_small_loss(const SddmmParams &a, double *lo
 }
 
 // One tile of T * E entries per block; blocks past the tiles zero the empty
-// segments.  A SMALL pass is complete in this launch: the block in which a
-// segment starts also adds its entries past the tile, and the loss is one
-// more block, the first.  out[s] = alpha sum w_p X[idx_p]; with DUAL also
+// segments.  A WHOLE pass is complete in this launch: the block in which a
+// segment starts also adds its entries past the tile, and the loss (of tiles of
+// one entry per thread) is one more block, the first.  out[s] = alpha sum w_p X[idx_p]; with DUAL also
 // sdd[pos_p] = sdd_alpha own[s] X[idx_p] and the loss sum w_p own[s] X[idx_p].
-template <int T, int E, bool DUAL, bool SMALL>
+template <int T, int E, bool DUAL, bool WHOLE>
 __global__ __launch_bounds__(T) void vec1_kernel(Vec1Params f) {
     constexpr int kTile = T * E, kWaves = T / kWave;
     const SgrParams &a = f.s;
     const int tid = threadIdx.x;
     int blk = blockIdx.x;
-    if constexpr (SMALL && DUAL) {
+    if constexpr (WHOLE && DUAL && E == 1) {
         if (f.loss && blk-- == 0) {
             vec1_small_loss<T>(f.entries, f.loss);
             return;
@@ -235,24 +235,24 @@ __global__ __launch_bounds__(T) void vec1_kernel(Vec1Params f) {
         before = 0.f;
         before_starts = false;
     }
-    // (a SMALL pass drops the parts of segments that start in earlier tiles)
+    // (a WHOLE pass drops the parts of segments that start in earlier tiles)
     if (!single && r[0] >= 0) {  // the first run ends in this thread
         const bool goes_on = prev == r[0];
         const float t = !goes_on ? first : (before_starts ? before : before + carry) + first;
         if (!goes_on || before_starts || in_tile) a.out[r[0]] = a.alpha * t;
-        else if (!SMALL) f.head[blk] = t;
+        else if (!WHOLE) f.head[blk] = t;
     }
     __shared__ float tail;
     __shared__ int tail_seg;
-    if (SMALL && tid == T - 1) tail_seg = -1;
+    if (WHOLE && tid == T - 1) tail_seg = -1;
     if (r[E - 1] >= 0) {
         const float t = starts ? sum : sum + carry;
         const bool here = starts || in_tile;
         if (next != r[E - 1]) {  // the last run ends with this thread
             if (here) a.out[r[E - 1]] = a.alpha * t;
-            else if (!SMALL) f.head[blk] = t;
+            else if (!WHOLE) f.head[blk] = t;
         } else if (tid == T - 1) {  // or goes on in the next tile
-            if (SMALL) {
+            if (WHOLE) {
                 tail = t;
                 tail_seg = here ? r[E - 1] : -1;
             } else {
@@ -261,7 +261,7 @@ __global__ __launch_bounds__(T) void vec1_kernel(Vec1Params f) {
             }
         }
     }
-    if constexpr (SMALL) {
+    if constexpr (WHOLE) {
         __syncthreads();
         if (tail_seg >= 0) {  // the rest of the segment open at the tile's end
             float s = 0.f;
@@ -324,12 +324,21 @@ __global__ __launch_bounds__(kBlock) void vec1_fix_kernel(Vec1Params f, int64_t 
     if (lane == 0) a.out[seg] = a.alpha * (f.tail[b] + s);
 }
 
-// Tiles of one pass.  A small one is complete in one launch (a combine and
-// its launch cost more than re-reading at most that many entries of crossing
-// segments, and one block streams that many for the loss in the time a second
-// launch takes).  Above, 256 threads of two entries while that does not give
-// every SIMD two waves, of eight (16-byte loads) from there on.
+// Tiles of one pass.  A small one is complete in one launch: a combine and
+// its launch cost more than re-reading the crossing segments, unless one block
+// has more than kVec1Tail entries of a segment to add, twice as many if it
+// gathers nothing for them (a row of 16K entries 10.5 us, with the combine 5.1), and, for a loss of its own that gathers two words
+// an entry, than streaming up to kVec1SmallLoss entries by one block (10K
+// entries 7.6 us, 16K 9.9; with the combine 7.2 and 7.4).  Above, 256 threads of
+// two entries while that does not give every SIMD two waves, of eight (16-byte
+// loads) from there on.  Those are complete in one launch too, up to kVec1Whole
+// entries, where no loss rides on the combine and every segment is short (SpMV
+// of 262K rows of about one entry 6.6 -> 4.8 us; of 20M entries 115 -> 123).
 constexpr int64_t kVec1Small = 16384;
+constexpr int64_t kVec1SmallLoss = 8192;
+constexpr int64_t kVec1Tail = 4096;
+constexpr int64_t kVec1Whole = int64_t(1) << 23;
+constexpr int32_t kVec1ShortItems = 256;
 constexpr int kVec1SmallThreads = 512;
 constexpr int64_t kVec1Short = int64_t(1) << 20;
 
@@ -344,11 +353,11 @@ int64_t vec1_max_tiles(int64_t nnz) {
     return std::max(ceil_div(n, vec1_tile(n)), ceil_div(few, vec1_tile(few)));
 }
 
-template <int T, int E, bool DUAL, bool SMALL>
+template <int T, int E, bool DUAL, bool WHOLE>
 static nsd_status vec1_launch(const Vec1Params &f, int probe_id, hipStream_t st) {
     const int64_t grid = f.s.item_blocks + ceil_div(f.s.plan.nempty, T) + (f.loss ? 1 : 0);
     probe_begin(probe_id, st);
-    vec1_kernel<T, E, DUAL, SMALL><<<(unsigned)grid, T, 0, st>>>(f);
+    vec1_kernel<T, E, DUAL, WHOLE><<<(unsigned)grid, T, 0, st>>>(f);
     probe_end(probe_id, st);
     return check_launch("vec1_kernel");
 }
@@ -359,10 +368,15 @@ static nsd_status vec1_run(Vec1Params f, int probe_id, LossJob job, hipStream_t 
     const int64_t tile = vec1_tile(a.nnz);
     const int64_t tiles = ceil_div(a.nnz, tile);
     a.item_blocks = (int32_t)tiles;
-    if (a.nnz <= kVec1Small && !job.p1) {
+    const int64_t longest = (int64_t)a.plan.longest_chunks * a.plan.item_len;
+    const int64_t small = job.loss && a.X ? kVec1SmallLoss : kVec1Small;
+    if (a.nnz <= small && longest <= (a.X ? 1 : 2) * kVec1Tail && !job.p1) {
         f.loss = job.loss;
         return vec1_launch<kVec1SmallThreads, 1, DUAL, true>(f, probe_id, st);
     }
+    if (!job.loss && a.nnz < kVec1Whole && a.plan.nlong == 0 && a.plan.item_len <= kVec1ShortItems)
+        return tile == 8 * kBlock ? vec1_launch<kBlock, 8, DUAL, true>(f, probe_id, st)
+                                  : vec1_launch<kBlock, 2, DUAL, true>(f, probe_id, st);
     f.head = a.part;
     f.tail = a.part + tiles;
     if (job.loss && !job.p1) {  // the pass's own loss

@@ -1,12 +1,17 @@
 """Passes of dense width 1 (SpMV, its transpose and VJP, the SMVM loss) at
-the edges of their tiles: one entry, one block's tile of 16,384 entries and a
-word around it, tiles of 512 and 2,048, segments that cross none, some and
-all tiles, runs of empty segments; against 64-bit sums of the same products.
+the edges of their dispatch and tiles: one entry, the sizes up to which a pass
+is complete in one launch of 512-entry tiles (16,384 entries; 8,192 with a loss
+that gathers both vectors), tiles of 512 and 2,048 above (from 2^20 entries on),
+patterns of short segments only, complete in one launch below 2^23 entries,
+segments that cross no tile, some and all, runs of empty segments; against
+64-bit sums of the same products.
 
-Bound: a product passes through at most 16 additions in its thread, 6 over
-the wave, 16 over the waves, and ceil(tiles / 64) + 6 over the tiles a segment
-crosses (below 64 in all here), each within 2^-24 of the sum of magnitudes,
-after two rounded products."""
+Bound, additions a product passes through.  Complete in one launch: 6 over the
+wave and 8 over the waves of its tile, 2 that join them, at most 9 strided ones of
+the segment's rest (4,096 entries by 512 threads), 6 and 8 to sum those, 1.  With
+a combine: 7 in the thread, 6, 4 and 2, then ceil(tiles / 64) + 7 over the tiles
+that a segment crosses, at most 2,048 here: 58.  Each is within 2^-24 of the sum
+of magnitudes; with the rounded products and the scale 61, below the 66 used."""
 import numpy as np
 import pytest
 import torch
@@ -97,3 +102,14 @@ def test_width_one(operand, kind, nnz, plans):
     t2 = v64 * x64[col] * g64[row]
     assert abs(loss2.item() - t2.sum()) <= 2.0 ** -23 * np.abs(t2).sum()
     close(dx, col, v64 * g64[row], ncols, "dH")
+
+
+@pytest.mark.parametrize("kind", ["short", "crossing", "one", "column"])
+@pytest.mark.parametrize("nnz", [4095, 4097, 8191, 8192, 8193, 12_289])
+def test_width_one_of_few_entries(operand, kind, nnz):
+    test_width_one(operand, kind, nnz, False)
+
+
+@pytest.mark.parametrize("nnz", [(1 << 23) - 1, (1 << 23) + 1])
+def test_width_one_of_short_rows(operand, nnz):
+    test_width_one(operand, "short", nnz, False)
