@@ -2,10 +2,10 @@
 // expansion, value permutation and CSR validation.
 //
 // Every ordering is a stable sort by key, done as least-significant-digit
-// radix sort: a sequence of stable counting sorts on 8-bit digits (histogram
-// per tile, one device-wide exclusive scan over [digit][tile], stable scatter
-// with wave-level match masks).  Ties keep their input order, so the results
-// are bit-exact and equal to a sequential stable sort.
+// radix sort: a sequence of stable counting sorts on digits of 8 to 10 bits
+// (histogram per tile, one device-wide exclusive scan over [digit][tile], stable
+// scatter with wave-level match masks).  Ties keep their input order, so the
+// results are bit-exact and equal to a sequential stable sort.
 #include <algorithm>
 
 #include "nsd_internal.hpp"
@@ -165,9 +165,8 @@ nsd_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *t
 constexpr int kSortRounds = 16;  // 64-element rounds per wave
 constexpr int kMaxPayloads = 3;
 
-// A pass sorts by a digit of 8 bits, or of up to 10 where that takes a pass
-// less (digit_bits): a pass moves every key and payload once whatever its
-// digit.  Sorts of kSortStreamMin elements and more take tiles of 8,192 by
+// A pass sorts by a digit of 8 to 10 bits (digit_bits): it moves every key and
+// payload once whatever its digit.  Sorts of kSortStreamMin elements and more take tiles of 8,192 by
 // 512 threads, so that a tile's run of one digit stays near a line; shorter
 // ones 4,096 by 256, enough tiles for all CUs.
 constexpr int kDigitBits = 8, kWideDigitBits = 10;
@@ -461,10 +460,17 @@ static int key_bits(int32_t max_key) {
     return bits;
 }
 
-// The digit of a sort by keys of `bits` bits: wide ones where they save a
-// third of the passes (9 to 10 bits, 17 to 20), the bits spread evenly.
+// The digit of a sort by keys of `bits` bits, spread evenly over the passes: 9
+// bits where they save a pass, 10 only where they save a third of them.
+// COO -> CSR on MI355X, passes of 8 bits against fewer of 9 or 10: 26 bits (4
+// passes, 3) 322 / 296 us for 1M entries, 1.25 / 1.16 ms for 9M; 34 bits (5, 4)
+// 324 / 295 us, 0.97 / 0.90 ms, 4.79 / 4.49 for 50M; but 30 bits (4, 3 of 10)
+// 0.91 / 0.93 ms for 8M and 5.86 / 5.85 for 50M, 40 (5, 4 of 10) 0.79 / 0.86 for
+// 8M and 4.22 / 4.38 for 50M.  One-payload sorts of 25 bits gain 7 to 12 %.
 static int digit_bits(int bits) {
-    const int64_t narrow = ceil_div(bits, kDigitBits), wide = ceil_div(bits, kWideDigitBits);
+    const int64_t narrow = ceil_div(bits, kDigitBits);
+    const int64_t nine = ceil_div(bits, kDigitBits + 1), wide = ceil_div(bits, kWideDigitBits);
+    if (nine < narrow) return (int)ceil_div(bits, nine);
     return 3 * wide <= 2 * narrow && bits > 0 ? (int)ceil_div(bits, wide) : kDigitBits;
 }
 

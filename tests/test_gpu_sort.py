@@ -77,3 +77,11 @@ def test_coo_to_csr_pair_keys(nsd, nrows, ncols, n):
     assert torch.equal(perm[:m], order[first].int())
     counts = torch.unique_consecutive(key, return_counts=True)[1]
     assert torch.equal(vout[:m], counts.float())
+
+
+@pytest.mark.parametrize("nrows,ncols", [(8000, 4097), (5000, 16_000), (100_000, 120_000),
+                                         (200_000, 250_000)])
+@pytest.mark.parametrize("n", [5000, 1 << 23])
+def test_coo_to_csr_nine_bit_digits(nsd, nrows, ncols, n):
+    """Pairs of 26, 27, 34 and 36 bits: digits of nine bits save a pass."""
+    test_coo_to_csr_pair_keys(nsd, nrows, ncols, n)
