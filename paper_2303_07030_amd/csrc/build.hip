@@ -18,14 +18,8 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
-struct OpSum {
-    static constexpr int kIdentity = 0;
-    __device__ static int apply(int a, int b) { return a + b; }
-};
-
 // Exclusive scan of one value per thread across the block; returns the
 // block total through *total.
-template <class Op>
 __device__ int block_exclusive_scan(int v, int *total) {
     __shared__ int wave_tot[kScanThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -34,93 +28,90 @@ __device__ int block_exclusive_scan(int v, int *total) {
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
         int t = __shfl_up(inc, d, kWave);
-        if (lane >= d) inc = Op::apply(t, inc);
+        if (lane >= d) inc += t;
     }
     int exc = __shfl_up(inc, 1, kWave);
-    if (lane == 0) exc = Op::kIdentity;
+    if (lane == 0) exc = 0;
     if (lane == kWave - 1) wave_tot[wave] = inc;
     __syncthreads();
-    int base = Op::kIdentity, all = Op::kIdentity;
+    int base = 0, all = 0;
 #pragma unroll
     for (int w = 0; w < kScanThreads / kWave; ++w) {
-        if (w < wave) base = Op::apply(base, wave_tot[w]);
-        all = Op::apply(all, wave_tot[w]);
+        if (w < wave) base += wave_tot[w];
+        all += wave_tot[w];
     }
     __syncthreads();
     *total = all;
-    return Op::apply(base, exc);
+    return base + exc;
 }
 
-template <class Op>
 __global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(const int32_t *in, int64_t n,
                                                                    int32_t *sums) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int s = Op::kIdentity;
+    int s = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i)
-        if (base + i < n) s = Op::apply(s, in[base + i]);
+        if (base + i < n) s += in[base + i];
     int total;
-    block_exclusive_scan<Op>(s, &total);
+    block_exclusive_scan(s, &total);
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-template <class Op>
 __global__ __launch_bounds__(kScanThreads) void scan_tile_kernel(const int32_t *in, int32_t *out,
                                                                  int64_t n, const int32_t *offs,
                                                                  int32_t *total_dev) {
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int v[kScanItems];
-    int s = Op::kIdentity;
+    int s = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
-        v[i] = base + i < n ? in[base + i] : Op::kIdentity;
-        s = Op::apply(s, v[i]);
+        v[i] = base + i < n ? in[base + i] : 0;
+        s += v[i];
     }
     int total;
-    const int pre = offs ? offs[blockIdx.x] : Op::kIdentity;
-    int run = Op::apply(pre, block_exclusive_scan<Op>(s, &total));
+    const int pre = offs ? offs[blockIdx.x] : 0;
+    int run = pre + block_exclusive_scan(s, &total);
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         if (base + i < n) out[base + i] = run;
-        run = Op::apply(run, v[i]);
+        run += v[i];
     }
     if (total_dev && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-        *total_dev = Op::apply(pre, total);
+        *total_dev = pre + total;
 }
 
 // A tile scan whose block first forms its own prefix from the tile sums of
 // the blocks before it (at most kScanTile of them): one level and one launch
 // fewer than scanning the sums separately.
-template <class Op>
 __global__ __launch_bounds__(kScanThreads) void scan_tile_prefix_kernel(const int32_t *in,
                                                                         int32_t *out, int64_t n,
                                                                         const int32_t *sums,
                                                                         int32_t *total_dev) {
-    int s = Op::kIdentity;
+    int s = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         const int j = threadIdx.x * kScanItems + i;  // tiles before this block, in order
-        if (j < (int)blockIdx.x) s = Op::apply(s, sums[j]);
+        if (j < (int)blockIdx.x) s += sums[j];
     }
     int pre;
-    block_exclusive_scan<Op>(s, &pre);  // pre = the sum over all of them
+    block_exclusive_scan(s, &pre);  // pre = the sum over all of them
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int v[kScanItems];
-    int t = Op::kIdentity;
+    int t = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
-        v[i] = base + i < n ? in[base + i] : Op::kIdentity;
-        t = Op::apply(t, v[i]);
+        v[i] = base + i < n ? in[base + i] : 0;
+        t += v[i];
     }
     int total;
-    int run = Op::apply(pre, block_exclusive_scan<Op>(t, &total));
+    int run = pre + block_exclusive_scan(t, &total);
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
         if (base + i < n) out[base + i] = run;
-        run = Op::apply(run, v[i]);
+        run += v[i];
     }
     if (total_dev && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-        *total_dev = Op::apply(pre, total);
+        *total_dev = pre + total;
 }
 
 size_t scan_ws_bytes(int64_t n) {
@@ -133,23 +124,22 @@ size_t scan_ws_bytes(int64_t n) {
     return c.bytes();
 }
 
-template <class Op>
 static nsd_status scan_level(const int32_t *in, int32_t *out, int64_t n, int32_t *total_dev,
                              Carver &c, hipStream_t st) {
     const int64_t tiles = ceil_div(n, kScanTile);
     if (tiles <= 1) {
-        scan_tile_kernel<Op><<<1, kScanThreads, 0, st>>>(in, out, n, nullptr, total_dev);
+        scan_tile_kernel<<<1, kScanThreads, 0, st>>>(in, out, n, nullptr, total_dev);
         return check_launch("scan_tile_kernel");
     }
     int32_t *sums = c.take<int32_t>(tiles);
-    scan_reduce_kernel<Op><<<tiles, kScanThreads, 0, st>>>(in, n, sums);
+    scan_reduce_kernel<<<tiles, kScanThreads, 0, st>>>(in, n, sums);
     NSD_TRY(check_launch("scan_reduce_kernel"));
     if (tiles <= kScanTile) {
-        scan_tile_prefix_kernel<Op><<<tiles, kScanThreads, 0, st>>>(in, out, n, sums, total_dev);
+        scan_tile_prefix_kernel<<<tiles, kScanThreads, 0, st>>>(in, out, n, sums, total_dev);
         return check_launch("scan_tile_prefix_kernel");
     }
-    NSD_TRY(scan_level<Op>(sums, sums, tiles, nullptr, c, st));
-    scan_tile_kernel<Op><<<tiles, kScanThreads, 0, st>>>(in, out, n, sums, total_dev);
+    NSD_TRY(scan_level(sums, sums, tiles, nullptr, c, st));
+    scan_tile_kernel<<<tiles, kScanThreads, 0, st>>>(in, out, n, sums, total_dev);
     return check_launch("scan_tile_kernel");
 }
 
@@ -157,7 +147,7 @@ static nsd_status scan_level(const int32_t *in, int32_t *out, int64_t n, int32_t
 nsd_status scan_exclusive(const int32_t *in, int32_t *out, int64_t n, int32_t *total_dev,
                           void *ws, hipStream_t st) {
     Carver c(ws);
-    return scan_level<OpSum>(in, out, n, total_dev, c, st);
+    return scan_level(in, out, n, total_dev, c, st);
 }
 
 // ------------------------------------------------------------ radix sort
@@ -205,18 +195,6 @@ __device__ __forceinline__ int key_digit(int32_t lo, int32_t hi, int lo_bits, in
     if (lo_bits == 0 || shift + bits <= lo_bits) return (int)((l >> shift) & mask);
     if (shift >= lo_bits) return (int)((h >> (shift - lo_bits)) & mask);
     return (int)(((l >> shift) | (h << (lo_bits - shift))) & mask);  // straddles both
-}
-
-// Workgroups go to the eight XCDs round-robin (block b on XCD b mod 8), each
-// XCD with its own L2.  This renumbers the blocks so that every XCD takes one
-// contiguous range of the tiles: neighbouring tiles write adjacent runs of
-// one output region, and with the renumbering those runs meet in one L2 and
-// leave it as whole lines instead of partial ones from eight L2s.
-__device__ __forceinline__ int64_t xcd_contiguous_tile() {
-    const int nb = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
-    int start = 0;
-    for (int y = 0; y < x; ++y) start += (nb - y + 7) / 8;  // blocks on XCDs before x
-    return start + b / 8;
 }
 
 // Digit counts of one tile.  Keys drawn from a skewed distribution share

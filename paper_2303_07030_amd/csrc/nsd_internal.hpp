@@ -96,6 +96,18 @@ __device__ __forceinline__ float lane_xor(float v) {
     }
 }
 
+// Workgroups go to the eight XCDs round-robin (block b on XCD b mod 8), each
+// XCD with its own L2.  This renumbers the blocks so that every XCD takes one
+// contiguous range of the tiles: neighbouring tiles write adjacent runs of
+// one output region, and with the renumbering those runs meet in one L2 and
+// leave it as whole lines instead of partial ones from eight L2s.
+__device__ __forceinline__ int64_t xcd_contiguous_tile() {
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
+    int start = 0;
+    for (int y = 0; y < x; ++y) start += (nb - y + 7) / 8;  // blocks on XCDs before x
+    return start + b / 8;
+}
+
 // Makes x a value that the compiler may not equate with its earlier self: what
 // follows from it is computed again (an addition, a shift) where it is needed
 // instead of kept in registers of its own across the phases of a kernel.

@@ -26,29 +26,13 @@
 
 namespace nsd {
 
-#ifndef NSD_PERM_TILE
-#define NSD_PERM_TILE 32768
-#endif
 constexpr int kPermThreads = 1024;
-constexpr int kPermTile = NSD_PERM_TILE;  // T = B, the LDS span of either pass (128 KiB)
-static_assert(kPermTile <= 65536, "local indices are 16-bit");
+constexpr int kPermBits = 15;              // log2 of the tile: a local index inside it
+constexpr int kPermTile = 1 << kPermBits;  // T = B, the LDS span of either pass (128 KiB)
 
 static int64_t perm_tiles(int64_t n) { return ceil_div(n, kPermTile); }
 
 // ------------------------------------------------------------- apply
-
-// Workgroups go to the eight XCDs round-robin (block b on XCD b mod 8), each
-// XCD with its own L2.  This renumbers the blocks so that every XCD takes one
-// contiguous range of the tiles: neighbouring tiles write adjacent runs of
-// one output region, and with the renumbering those runs meet in one L2 and
-// leave it as whole lines instead of partial ones from eight L2s.
-__device__ __forceinline__ int64_t xcd_contiguous_tile() {
-    const int nb = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
-    int start = 0;
-    for (int y = 0; y < x; ++y) start += (nb - y + 7) / 8;  // blocks on XCDs before x
-    return start + b / 8;
-}
-
 
 // Each thread handles kPermPer elements of its tile, strided by the block
 // size, in batches of kPermBatch whose loads are all issued before any is
@@ -147,8 +131,6 @@ __global__ __launch_bounds__(kPermThreads) void perm_pass2_kernel(int64_t n,
 // side's, or back), so one partition makes both plans: two of 50M elements
 // 1.73 -> 0.92 ms on MI355X.
 
-constexpr int kPermBits = 15;  // log2 of the tile: a near offset inside it
-static_assert(kPermTile == 1 << kPermBits, "local offsets take kPermBits bits");
 constexpr int kPermWaves = kPermThreads / kWave;
 
 // A far index as counted and placed: out of range ones (reported through
