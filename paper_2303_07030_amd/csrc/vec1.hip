@@ -11,8 +11,9 @@
 // are a segmented scan: in the thread, over the wave's lanes, over the block's
 // waves.  A segment inside one tile is written directly; one that crosses
 // tiles leaves its first tile's part in tail[] and each later tile's in
-// head[], added in tile order by the combine.  Everything is summed in a fixed
-// order, so results are the same from run to run.  The SMVM loss of 20M
+// head[], added in tile order by the combine, or is finished by the block in
+// which it starts (vec1_run says when).  Everything is summed in a fixed order,
+// so results are the same from run to run.  The SMVM loss of 20M
 // entries takes 0.26 ms: 0.13 the sampled product (20M gathers of a word of x,
 // a 128-byte line from L2 each: the L2's rate), 0.09 the values' move to CSC
 // order, 0.03 their sums (5.4 TB/s).

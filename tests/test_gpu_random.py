@@ -17,8 +17,8 @@ from test_gpu_parity import (check_cp, check_cpn, check_frob, check_mf, dev, hos
 
 pytestmark = pytest.mark.gpu
 
-# 13, 30 and 50 take scalar-lane slots of 16, 32 and 64 lanes on the fused
-# passes; 70, 264 and 300 are wider than a fused slot
+# 2, 3, 5 and 13 take one column per lane, 30, 50 and 70 four with a last lane
+# that steps back; 264 and 300 are wider than a fused slot
 KS = [1, 2, 3, 5, 8, 12, 13, 16, 24, 30, 32, 48, 50, 64, 70, 100, 128, 200, 256, 264, 300]
 ITEM_LENS = [None, 2, 3, 4, 7, 8, 16, 33, 64]
 

@@ -1,8 +1,7 @@
 """Every fused loss at any dense width: k above what one slot of the fused
-kernels holds (256 columns with 16-byte aligned rows, 64 otherwise), widths
-that are not a multiple of 4, and rows that are not 16-byte aligned, against
-the fp64 oracle; and the scalar-lane slots of 16, 32 and 64 lanes that
-widths in 9..63 with k % 4 != 0 take on the fused passes.
+kernels holds (256 columns), widths that are not a multiple of 4, and rows
+that are not 16-byte aligned, against the fp64 oracle: one column per lane in
+slots of 16 (13), four with a last lane that steps back (30, 50, 70).
 """
 import numpy as np
 import pytest
@@ -15,8 +14,8 @@ from test_gpu_parity import (check_cp, check_cpn, check_frob, dev, edge_pattern,
 
 pytestmark = pytest.mark.gpu
 
-WIDE = [257, 300, 513, 70]     # above a fused slot; 70: scalar lanes above 64
-SCALAR = [13, 30, 50]          # scalar lanes, slots of 16, 32 and 64 lanes
+WIDE = [257, 300, 513, 70]     # above a fused slot; 70: ragged quads of 32 lanes
+SCALAR = [13, 30, 50]          # one column per lane; ragged quads of 8 and 16 lanes
 
 
 @pytest.fixture(scope="module")
@@ -87,7 +86,7 @@ def test_loss_mf_any_width(nsd, operand, orc, k, with_valT):
 
 @pytest.mark.parametrize("k", [128, 256])
 def test_loss_mf_unaligned_rows(nsd, operand, orc, k):
-    # a multiple of 4 that a fused slot holds only with 16-byte aligned rows
+    # whole quads off their 16-byte lines
     nrows, ncols, rowptr, colind, val, U, V = mf_case(k, seed=17)
     A = operand(nrows, ncols, rowptr, colind, val, k_hint=k)
     loss = torch.empty(1, dtype=torch.float64, device="cuda")
