@@ -40,7 +40,7 @@ namespace nsd {
 // the per-batch arithmetic shared by both ways of fetching entry metadata.
 template <int KIND, int VEC, int G, int U, bool RAG>
 struct DualSlot {
-    static constexpr bool kLongBatch = true;
+    static constexpr bool kLongBatch = VEC > 1 || KIND == kDualMf;
     const DualPass &m;
     int64_t s, k, b0;  // k: the stride of the dense rows
     int lane, g, col, dup;

@@ -120,7 +120,10 @@ __device__ __forceinline__ void walk_item(const SgrParams &a, int64_t a0, int64_
             }
             // A dual pass's batch of four entries is hundreds of instructions;
             // four copies of it cost the column pass of k = 64 4 % (51.2 ->
-            // 53.2 us).  Left to the compiler otherwise: the copies of two
+            // 53.2 us), and the factorisation of k = 13, one column a lane, 13 %
+            // (1M entries 61.3 -> 69.4; 100K 15.6 -> 15.1).  The linear passes of
+            // one column a lane keep them (100K entries, k = 13: 14.1 -> 13.4 us).
+            // Left to the compiler otherwise: the copies of two
             // entries' batches that it makes gain 4 % (a GNN layer of k = 32:
             // 51.8 -> 49.8 us), and of full-wave slots it makes none, but told
             // so it ran the GNN layer's pass of k = 256 2 % slower.  (A
