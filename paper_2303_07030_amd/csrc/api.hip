@@ -59,7 +59,7 @@ static size_t part_region_bytes(const nsd_csr *A, const nsd_csc *At, int k) {
 }
 
 static size_t loss_part_count(const nsd_csr *A, const nsd_csc *At, int k) {
-    int64_t m = std::max<int64_t>(1, frob_row_blocks(A->plan, k));
+    int64_t m = std::max<int64_t>(1, frob_row_blocks(A->plan, A->nnz, k));
     for (int kk : {k, 1})
         for (bool whole : {true, false}) m = std::max(m, sddmm_shape(A->nnz, kk, whole).nblocks);
     if (At) {

@@ -265,7 +265,7 @@ constexpr int dual_unroll() {
 }
 
 int64_t dual_blocks(const nsd_plan *const *plans, int npass, int64_t nnz, int k) {
-    const WidthPlan wp = narrow_plan(k, false);  // the layout of more blocks
+    const WidthPlan wp = narrow_plan(k, false, scalar_width(nnz, k));  // the layout of more blocks
     const int slots = kBlock / wp.g;
     int64_t n = 0;
     for (int i = 0; i < npass; ++i)
@@ -310,7 +310,7 @@ static nsd_status launch_dual(DualParams f, int probe_id, LossJob job, hipStream
 
 template <int KIND>
 struct DualLauncher {
-    static constexpr int kMin = KIND == kDualMf ? 1 : 2, kScalar = kScalarWidth, kRagged = kScalarWidth + 1;
+    static constexpr int kMin = KIND == kDualMf ? 1 : 2, kScalar = kColdScalarWidth, kRagged = kScalarWidth + 1;
     DualParams f;
     int probe_id;
     LossJob job;
@@ -339,7 +339,7 @@ nsd_status dual_fused(int kind, DualParams f, int probe_id, LossJob job, hipStre
     bool whole = true;
     for (int i = 0; i < f.npass; ++i)
         whole = whole && whole_quads(k, {f.pass[i].own, f.pass[i].s.X, f.pass[i].s.out});
-    const WidthPlan wp = narrow_plan(k, whole);
+    const WidthPlan wp = narrow_plan(k, whole, scalar_width(f.pass[0].s.nnz, k));
     if (kind == kDualMf) {
         DualLauncher<kDualMf> fn{f, probe_id, job, st};
         return dispatch_width(wp, fn);

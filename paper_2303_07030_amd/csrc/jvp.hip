@@ -191,7 +191,8 @@ constexpr int kJvpScalarWidth = 32;
 
 static WidthPlan jvp_plan(int k, int64_t nnz, std::initializer_list<const void *> rows) {
     const bool scalar = nnz < (1 << 14) || (nnz >= (1 << 17) && nnz < (1 << 20));
-    return narrow_plan(k, whole_quads(k, rows), scalar ? kJvpScalarWidth : kScalarWidth);
+    return narrow_plan(k, whole_quads(k, rows),
+                       scalar ? kJvpScalarWidth : scalar_width(nnz, k));
 }
 
 template <int MB>

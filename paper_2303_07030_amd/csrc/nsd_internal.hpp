@@ -228,6 +228,21 @@ inline bool whole_quads(int k, std::initializer_list<const void *> rows) {
 // items per wave as one of sixteen, each waiting for the others' segment ends.
 constexpr int kScalarWidth = 16;
 
+// Up to kColdScalarWidth columns from kColdFloats gathered floats on (twice as
+// many for multiples of four off 16-byte addresses): the rows come from beyond
+// the L2s then, and a slot of eight lanes waits for its wave's seven others.
+// Measured likewise, each with its items: k = 30, 9.5M entries, a bilinear step
+// 505 / 557, the factorisation 688 / 762; 30M, 1433 / 1614 and 2120 / 2374; at
+// k = 18, 15M 715 / 694 and 973 / 956, 30M 1348 / 1356 and 1807 / 1907; at k = 20
+// and 28 off 16 bytes, 15M 881 and 904 / 762 and 857, 30M 1545 and 1574 / 1592 and
+// 1791.
+constexpr int kColdScalarWidth = 32;
+constexpr int64_t kColdFloats = int64_t(1) << 28;
+
+inline int scalar_width(int64_t nnz, int k) {
+    return nnz * k >= (k % 4 ? 1 : 2) * kColdFloats ? kColdScalarWidth : kScalarWidth;
+}
+
 inline WidthPlan narrow_plan(int k, bool whole, int scalar = kScalarWidth) {
     return k <= scalar && !whole ? lane_plan(k, 1) : width_plan(k);
 }

@@ -354,7 +354,7 @@ nsd_status nsd_plan_item_len(int32_t nnz, int32_t k, int32_t *item_len) {
     // one slot of a wave (a slot covers min(k, 256) columns); measured on
     // MI355X this is within 2% of the best length for every workload shape
     // tried (1M to 60M entries, k = 32 to 256)
-    const WidthPlan wp = narrow_plan(k, k % 4 == 0);
+    const WidthPlan wp = narrow_plan(k, k % 4 == 0, scalar_width(nnz, k));
     const int64_t slots = 32768LL * (kWave / wp.g);
     int32_t L = 16;
     while (L < 256 && (int64_t)L * 2 * slots <= nnz) L <<= 1;
@@ -367,6 +367,10 @@ nsd_status nsd_plan_item_len(int32_t nnz, int32_t k, int32_t *item_len) {
         L = 2;
         while (L < 16 && (int64_t)L * 2 * fill <= nnz) L <<= 1;
     }
+    // the narrow slots of widths that are no multiple of four: longer items
+    // spread a wave's metadata reads over more lines (30M entries, k = 50, us: a
+    // bilinear step 1738 at 32 against 1893 at 128, the factorisation 2807 / 2936)
+    if (wp.ragged && wp.g <= 16) L = std::min(L, 16 + wp.g);
     *item_len = L;
     return NSD_OK;
 }

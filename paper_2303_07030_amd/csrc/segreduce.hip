@@ -77,7 +77,7 @@ static nsd_status launch_sgr_vg(SgrParams a, hipStream_t st) {
 }
 
 struct SgrLauncher {
-    static constexpr int kMin = 2, kScalar = kScalarWidth, kRagged = kScalarWidth + 1;
+    static constexpr int kMin = 2, kScalar = kColdScalarWidth, kRagged = kScalarWidth + 1;
     SgrParams a;
     hipStream_t st;
     template <int VEC, int G, bool RAG>
@@ -92,7 +92,8 @@ nsd_status segreduce(SgrParams a, hipStream_t st) {
     }
     if (a.k == 1) return vec1_reduce(a, LossJob{}, st);
     SgrLauncher f{a, st};
-    return dispatch_width(narrow_plan(a.k, whole_quads(a.k, {a.X, a.out})), f);
+    const bool whole = whole_quads(a.k, {a.X, a.out});
+    return dispatch_width(narrow_plan(a.k, whole, scalar_width(a.nnz, a.k)), f);
 }
 
 // ------------------------------------------------------------------ SDDMM
@@ -394,14 +395,14 @@ static nsd_status launch_frob(FrobParams f, hipStream_t st) {
     return dual_fused(kDualLin, d, NSD_KERNEL_FROB_COL, LossJob{}, st);
 }
 
-int64_t frob_row_blocks(const nsd_plan &rows, int k) {
-    const WidthPlan wp = narrow_plan(k, false);  // the layout of more blocks
+int64_t frob_row_blocks(const nsd_plan &rows, int64_t nnz, int k) {
+    const WidthPlan wp = narrow_plan(k, false, scalar_width(nnz, k));  // the layout of more blocks
     const int slots = kBlock / wp.g;
     return ceil_div(rows.nitems, slots) + ceil_div(rows.nempty, slots);
 }
 
 struct FrobLauncher {
-    static constexpr int kMin = 2, kScalar = kScalarWidth, kRagged = kScalarWidth + 1;
+    static constexpr int kMin = 2, kScalar = kColdScalarWidth, kRagged = kScalarWidth + 1;
     FrobParams f;
     hipStream_t st;
     template <int VEC, int G, bool RAG>
@@ -411,7 +412,7 @@ struct FrobLauncher {
 nsd_status frob_fused(FrobParams f, hipStream_t st) {
     FrobLauncher fn{f, st};
     const bool whole = whole_quads(f.rows.k, {f.rows.X, f.rows.out, f.cols.s.out});
-    return dispatch_width(narrow_plan(f.rows.k, whole), fn);
+    return dispatch_width(narrow_plan(f.rows.k, whole, scalar_width(f.rows.nnz, f.rows.k)), fn);
 }
 
 }  // namespace nsd

@@ -156,7 +156,7 @@ inline WidthPlan cp_plan(int rank, bool whole, int64_t nnz, int L) {
 int64_t cp_blocks(const nsd_plan *plans, int rank);
 nsd_status cp_fused(CpParams f, double *loss, hipStream_t st);
 
-int64_t frob_row_blocks(const nsd_plan &rows, int k);
+int64_t frob_row_blocks(const nsd_plan &rows, int64_t nnz, int k);
 nsd_status frob_fused(FrobParams f, hipStream_t st);
 
 SddmmShape sddmm_shape(int64_t nnz, int k, bool whole);

@@ -291,3 +291,71 @@ def test_tangents_of_more_entries(nsd, k, nnz):
         D, d = mat(dval[t]), dB[t].astype(np.float64)
         assert_mag_close(host(dC[t]), D @ b + S @ d, abs(D) @ abs(b) + abs(S) @ abs(d),
                          what=f"dC[{t}]")
+
+
+@pytest.mark.parametrize("k, over", [(31, -9), (31, 9), (17, 9)])
+def test_cold_operands(nsd, k, over):
+    """One column a lane up to 32 columns from 2^28 gathered floats on, in every
+    pass of a matrix."""
+    from paper_2303_07030_amd.operand import DeviceCsr
+    rng = np.random.default_rng(k)
+    nrows, ncols, nnz = 300_000, 250_000, (1 << 28) // k + over
+    rows, rowptr, cols, val = large_pattern(rng, nrows, ncols, nnz)
+    A = DeviceCsr(nrows, ncols, rowptr, cols, val, k_hint=k)
+    H, G = (rng.standard_normal((n, k)).astype(np.float32) for n in (ncols, nrows))
+    r, c, v, h, g = (torch.from_numpy(x).cuda() for x in (rows, cols, val, H, G))
+    r, c = r.long(), c.long()
+
+    def reduce(n, at, w, x, idx):  # sum of w_p x[idx_p] at at_p, and its magnitude, in fp64
+        s, m = (torch.zeros((n, k), dtype=torch.float64, device="cuda") for _ in range(2))
+        for p in torch.arange(nnz, device="cuda").split(1 << 20):
+            t = w[p].double()[:, None] * x[idx[p]].double()
+            s.index_add_(0, at[p], t)
+            m.index_add_(0, at[p], t.abs())
+        return host(s), host(m)
+
+    def dots(x, y):
+        s, m = (torch.empty(nnz, dtype=torch.float64, device="cuda") for _ in range(2))
+        for p in torch.arange(nnz, device="cuda").split(1 << 20):
+            t = x[r[p]].double() * y[c[p]].double()
+            s[p], m[p] = t.sum(1), t.abs().sum(1)
+        return s, m
+
+    ws, loss = A.workspace(k), torch.empty(1, dtype=torch.float64, device="cuda")
+    C, dC, dH = (empty_offset((n, k)) for n in (nrows, nrows, ncols))
+    dA = torch.full((nnz,), np.nan, device="cuda")
+    d, dm = dots(g, h)
+    fwd, col = reduce(nrows, r, v, h, c), reduce(ncols, c, v, g, r)
+
+    nsd.nsd_loss_bilinear(A.desc, A.csc, dev_offset(H), dev_offset(G), k, 0.5, loss, dA, dH, ws)
+    assert_mag_close(host(loss)[0], host((v * d).sum()), host((v.abs() * dm).sum()), what="loss")
+    assert_mag_close(host(dA), 0.5 * host(d), 0.5 * host(dm), what="dA")
+    assert_mag_close(host(dH), 0.5 * col[0], 0.5 * col[1], what="dH")
+
+    nsd.nsd_spmm(A.desc, h, k, C, ws)
+    assert_mag_close(host(C), *fwd, what="spmm")
+
+    wj = torch.empty(nsd.nsd_spmm_jvp_batch_workspace_size(A.desc, k), dtype=torch.uint8,
+                     device="cuda")
+    nsd.nsd_spmm_jvp_batch(A.desc, 1, v.neg()[None], h, 2 * h[None], k, C, dC[None], wj)
+    assert_mag_close(host(C), *fwd, what="C")
+    assert_mag_close(host(dC), fwd[0], 3 * fwd[1], what="dC")
+
+    B, dB = dev_offset(H), empty_offset((ncols, k))
+    nsd.nsd_loss_frob_spmm(A.desc, A.csc, B, k, 1.0, C, loss, dA, dB, ws)
+    cd = C.double()
+    assert_mag_close(host(C), *fwd, what="C of the loss")
+    assert_mag_close(host(loss)[0], host(0.5 * (cd * cd).sum()), host(0.5 * (cd * cd).sum()),
+                     what="half square")
+    s, m = dots(C, h)
+    assert_mag_close(host(dA), host(s), host(m), what="dA of the half square")
+    assert_mag_close(host(dB), *reduce(ncols, c, v, C, r), what="dB of the half square")
+
+    dU, dV = (empty_offset((n, k)) for n in (nrows, ncols))
+    nsd.nsd_loss_mf(A.desc, A.csc, A.values_in_csc_order(), dev_offset(G), dev_offset(H), k, 1.0,
+                    loss, dU, dV, ws)
+    res, mag = v - d, v.abs() + dm
+    assert_mag_close(host(loss)[0], host((res * res).sum()), host((mag * mag).sum()), what="squares")
+    for got, n, at, x, idx in ((dU, nrows, r, h, c), (dV, ncols, c, g, r)):
+        assert_mag_close(host(got), -2 * reduce(n, at, res, x, idx)[0],
+                         2 * reduce(n, at, mag, x.abs(), idx)[1], what="factor gradient")

@@ -34,3 +34,15 @@ def test_width_one_partials_follow_the_entries(item_len, nitems, csc):
     A.plan = At.plan = plan
     one, two = (nsd.nsd_workspace_size(A, At if csc else None, k) for k in (1, 2))
     assert one <= two + 2 * 16 * (nnz // 2048) + 1024
+
+
+def test_item_length_hint():
+    """Items of the narrow slots of widths that are no multiple of four stay
+    short; those of wider ones and of one column a lane go with the entries."""
+    for k in range(1, 65):
+        lens = [nsd.nsd_plan_item_len(1 << p, k) for p in range(31)]
+        assert min(lens) >= 2 and max(lens) <= 256
+        assert nsd.nsd_plan_item_len(2**30, k) == (32 if k > 32 and k % 4 else 256)
+    # one column a lane from 2^28 gathered floats on
+    assert nsd.nsd_plan_item_len((1 << 28) // 31, 31) == 24
+    assert nsd.nsd_plan_item_len((1 << 28) // 31 + 1, 31) == 128
