@@ -146,9 +146,11 @@ constexpr int kCpScalarWidth = 32;
 // the quads win down to the narrowest ranks where there is work for them; one
 // column per lane wins where a wave's items are few (cp3 of 20K entries, rank 7,
 // us: 8.4 against 10.9; rank 13 9.2 / 9.7; rank 25 of 3K 8.6 / 9.0) or long (10M
-// entries, rank 5, items of 12: 534 / 601; rank 10 of 24: 688 / 897).
+// entries, rank 5, items of 12: 534 / 601; rank 10 of 24: 688 / 897), and at
+// ranks 4 and 8, off 16-byte addresses here, where it leaves no lane idle (1M
+// entries 43 / 48 and 53 / 56; cp4 of 10M, rank 8, 775 / 848).
 inline WidthPlan cp_plan(int rank, bool whole, int64_t nnz, int L) {
-    const bool scalar = rank <= 8    ? L > 8 || nnz < (1 << 18)
+    const bool scalar = rank <= 8    ? rank % 4 == 0 || L > 8 || nnz < (1 << 18)
                         : rank <= 16 ? L > 16 || nnz < (1 << 15)
                                      : nnz < (1 << 13);
     return narrow_plan(rank, whole || !scalar, kCpScalarWidth);

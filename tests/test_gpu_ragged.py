@@ -12,7 +12,8 @@ import torch
 
 from helpers import assert_mag_close
 from test_gpu_parity import (check_cp, check_cpn, check_frob, dev, edge_pattern, host,
-                             oracle_dok, run_bilinear, run_cp, run_cpn, run_frob)
+                             in_input_order, oracle_dok, run_bilinear, run_cp, run_cpn,
+                             run_frob)
 from test_gpu_wide import check_mf_all, cp_case, dev_offset, empty_offset, mf_case
 
 pytestmark = pytest.mark.gpu
@@ -221,6 +222,21 @@ def test_cp_of_more_entries(nsd, orc, rank, nnz):
          for n, d in enumerate(dims)]
     X = DeviceCooN(dims, coords, val, item_len=8, fibers=True)
     check_cpn(orc, dims, coords, val, F, rank, run_cpn(nsd, X, F, rank, seed=0.5), seed=0.5)
+
+
+@pytest.mark.parametrize("rank", [4, 8, 12])
+def test_cp_off_lines_of_more_entries(nsd, orc, rank):
+    """Rows of whole quads off their 16-byte lines: one column a lane at ranks 4
+    and 8, quads at 12."""
+    from paper_2303_07030_amd.operand import DeviceCoo3
+    dims, i, j, l, val, F = cp_case(rank, dims=(90, 70, 120), nnz=(1 << 18) + 5)
+    X = DeviceCoo3(dims, i, j, l, val, rank_hint=rank)
+    loss = torch.empty(1, dtype=torch.float64, device="cuda")
+    dX, dF = torch.full((X.nnz,), np.nan, device="cuda"), [empty_offset((d, rank)) for d in dims]
+    nsd.nsd_loss_cp(X.desc, *[dev_offset(f) for f in F], rank, 0.75, loss, dX, *dF,
+                    X.workspace(rank))
+    got = host(loss)[0], in_input_order(X, host(dX)), [host(t) for t in dF]
+    check_cp(orc, dims, i, j, l, val, F, rank, got, seed=0.75)
 
 
 @pytest.mark.parametrize("k", [17, 31, 32])
